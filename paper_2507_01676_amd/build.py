@@ -19,6 +19,10 @@ ARCH = "gfx950"
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract=off",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-I", os.path.join(ROOT, "include")]
+# gather.hip's control flow is wave-uniform: leave it as written instead of turning every branch
+# into the flag-guarded form that divergent branches need (a compare, a jump and the additions per
+# instruction of a step, against about twenty instructions)
+GATHER_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-Wall"]
 
 
@@ -76,7 +80,7 @@ def build(verbose: bool = False) -> str:
     for ks in GATHER_STEPS:
         for part in range(GATHER_PARTS):
             o = os.path.join(BUILD, f"gather_{part}_k{ks}.o")
-            cmds.append([hipcc, *HIP_FLAGS, f"-DEMBX_GPART={part}", f"-DEMBX_GKS={ks}", "-c",
+            cmds.append([hipcc, *HIP_FLAGS, *GATHER_FLAGS, f"-DEMBX_GPART={part}", f"-DEMBX_GKS={ks}", "-c",
                          os.path.join(CSRC, "gather.hip"), "-o", o])
             objs.append(o)
     o = os.path.join(BUILD, "api.o")

@@ -313,7 +313,9 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
     return true;
   };
   const char* env_kernel = std::getenv("EMBX_GATHER_KERNEL");
+  // (the kernel offsets a few samples' outputs in 32 bits)
   bool wave_gather = (G0 == 16 || G0 == 32 || G0 == 64) && gather_only(p->plan) &&
+                     static_cast<int64_t>(num_tables) * embedding_dim < (int64_t(1) << 28) &&
                      !(env_kernel && std::strcmp(env_kernel, "classic") == 0);
   const int block = kBlock;
   if (wave_gather) {
@@ -487,6 +489,26 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
   // 119.1 us; workload 2, single-lookup bags only, 5.30 / 5.36 / 5.51 us.
   // EMBX_GATHER_STEPS = 12, 13 or 16 overrides it.
   int ksteps = 12;
+  // Bags per chunk of worker w's multi-lookup items for steps of N lookups (item_cb); at most
+  // 64, the bag ends a wavefront holds.
+  std::vector<int32_t> item_cb(items.size(), 1);
+  auto multi_lookup = [&](const DevItem& d) { return d.strat == S_GATHER && stats[d.table].max_pooling != 1; };
+  auto bag_lookups = [&](const DevItem& d) { return std::max(1.0, stats[d.table].mean_pooling); };
+  auto wave_chunks = [&](int w, double N) {
+    const int nwaves = block / 64;
+    double W = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      const DevItem& d = items[i];
+      if (!multi_lookup(d)) continue;
+      const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+      W += static_cast<double>(nb) * bag_lookups(d);
+    }
+    const double target = wave_chunk_override > 0.0 ? wave_chunk_override
+                                                    : std::max(2.0 * N, W / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
+      if (multi_lookup(items[i]))
+        item_cb[i] = static_cast<int32_t>(std::min(64.0, std::max(1.0, std::floor(target / bag_lookups(items[i])))));
+  };
   if (wave_gather) {
     const char* env_steps = std::getenv("EMBX_GATHER_STEPS");
     if (env_steps && *env_steps) {
@@ -498,27 +520,16 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
         return EMB_ERR_INVALID_ARGUMENT;
       }
     } else {
-      const int nwaves = block / 64;
       double best = -1.0;
       for (int cand : kGatherStepChoices) {
         const double N = static_cast<double>(cand) * (64 / p->G);
         double rounds = 0.0;
         for (int w = 0; w < K; ++w) {
-          double Ws = 0.0;
+          wave_chunks(w, N);
           for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
             const DevItem& d = items[i];
-            if (d.strat != S_GATHER || stats[d.table].max_pooling == 1) continue;
-            const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k -
-                               (static_cast<int64_t>(d.j) * max_batch) / d.k;
-            Ws += static_cast<double>(nb) * std::max(1.0, stats[d.table].mean_pooling);
-          }
-          const double target = wave_chunk_override > 0.0 ? wave_chunk_override
-                                                          : std::max(2.0 * N, Ws / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
-          for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
-            const DevItem& d = items[i];
-            if (d.strat != S_GATHER || stats[d.table].max_pooling == 1) continue;
-            const double s_t = std::max(1.0, stats[d.table].mean_pooling);
-            const double cb = std::max(1.0, std::floor(target / s_t));
+            if (!multi_lookup(d)) continue;
+            const double s_t = bag_lookups(d), cb = item_cb[i];
             const double nc = std::ceil(static_cast<double>((static_cast<int64_t>(max_batch) + d.k - 1) / d.k) / cb);
             rounds += nc * std::ceil(cb * s_t / N);
           }
@@ -572,11 +583,8 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
       // of a SW's time and the worker's tail is up to one chunk, so ~sqrt(5 W / NSW)
       // lookups per chunk balances the two; measured, chunks past ~128 lookups lose again
       // (the SWs then work on fewer tables at a time), hence the cap
-      const double wstep = static_cast<double>(ksteps) * (64 / p->G);   // lookups of one wave kernel step
-      const double target =
-          !wave_gather ? std::min(128.0, std::max(8.0, std::floor(std::sqrt(5.0 * Ws / nsw))))
-          : wave_chunk_override > 0.0 ? wave_chunk_override
-                                      : std::max(2.0 * wstep, Ws / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
+      const double target = std::min(128.0, std::max(8.0, std::floor(std::sqrt(5.0 * Ws / nsw))));
+      if (wave_gather) wave_chunks(w, static_cast<double>(ksteps) * (64 / p->G));
       const double wtarget = std::min(wave_chunk, std::max(1.0, std::floor(Ww / nwaves)));
       gr_ptr[w] = static_cast<int32_t>(gr.size());
       int64_t base[3] = {0, 0, 0};
@@ -587,6 +595,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
           if (d.strat != S_GATHER || class_of(d) != cls) continue;
           const double s_t = std::max(1.0, stats[d.table].mean_pooling);
           const int32_t cb = cls == 1 ? (wave_gather ? ksteps * (64 / p->G) : kChunkSingle)
+                             : cls == 2 && wave_gather ? item_cb[i]
                                       : static_cast<int32_t>(std::max(1.0, std::floor((cls == 0 ? wtarget : target) / s_t)));
           const int64_t nc = (slice_bags_any(d) + cb - 1) / cb;
           if (nc == 0) continue;

@@ -5,10 +5,15 @@
 // The unit of work is a wavefront, and every decision it takes is wave-uniform: which
 // chunk of bags it walks, where a step starts and ends, where each bag ends.  So the
 // control lives in scalar registers and the vector registers hold only row data, the
-// accumulators and one index per lane (92-128 VGPRs with kSteps = 12-16 rows in flight
+// accumulators and one index per lane (86-118 VGPRs with kSteps = 12-16 rows in flight
 // per SW: one 1024-thread workgroup per CU, 4 wavefronts per SIMD; measured, 12 in flight
 // at that occupancy beats 6 or 8 at two workgroups per CU).  The file is built once per
 // kSteps (EMBX_GKS = 12, 13, 16) and a plan picks the one whose steps its chunks fill best.
+//
+// What bounds it: instruction issue on short bags, the vector memory pipe on long ones (at
+// 131M lookups of 512-byte rows its address unit is busy 88% of the time), and HBM writes
+// of the pooled rows (without them, 3.4M fp16 lookups of 256 bytes would take 64 us, not
+// 105).  Hence scalar control that costs three instructions per row load (see Multi).
 //
 // A wavefront is S = 64 / G sub-wavefronts (SWs) of G lanes; lane i of a SW covers bytes
 // [16 i, 16 i + 16) of a row.  A step covers N = S * kSteps consecutive lookups of the
@@ -28,8 +33,9 @@
 // output (no reduction); a bag that holds more lookups at run time is summed on a slow
 // path, so any batch stays correct.
 //
-// An id outside [0, rows) adds nothing: it is counted, replaced by row 0 for the load,
-// and the loaded value is zeroed (a step with no such id skips that check).
+// An id outside [0, rows) adds nothing: it is counted, and its load goes past the table's
+// descriptor, which returns zeros without an access (tables of 4 GiB or more, read with
+// 64-bit addresses, load row 0 and clear it).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -42,9 +48,6 @@
 #endif
 #ifndef EMBX_GKS
 #define EMBX_GKS 12
-#endif
-#ifndef EMBX_NT_IDS
-#define EMBX_NT_IDS 0
 #endif
 #define EMBX_HAS_GPART(p) (EMBX_GPART < 0 || EMBX_GPART == (p))
 
@@ -65,13 +68,20 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ i32x4 buffer_load_row(i32x4 rsrc, int vindex, int voffset, int soffset, int aux)
     __asm("llvm.amdgcn.struct.buffer.load.v4i32");
 
-namespace {
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
+// raw buffer stores: base + voffset, dropped where voffset runs past num_records
+__device__ void buffer_store_f32(float v, i32x4 rsrc, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.f32");
+__device__ void buffer_store_f32x2(f32x2 v, i32x4 rsrc, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.v2f32");
+__device__ void buffer_store_f32x4(f32x4 v, i32x4 rsrc, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.v4f32");
+
+namespace {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSteps = EMBX_GKS;   // row loads in flight per lane per step (one build per value)
 static_assert(kSteps >= 1 && kSteps <= 16, "one id per lane of a row of 16 for each step");
@@ -86,7 +96,6 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
-constexpr int64_t kNoEnd = INT64_MAX;
 
 // Buffer descriptor of a table: rows of R bytes from base; num_records = rows (the
 // structured range check compares the row index).  Configuration dword for gfx9:
@@ -107,15 +116,11 @@ __device__ __forceinline__ int row_bcast(int v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + U, 0xF, 0xF, true);
 }
 
+// a value that is the same in every lane, kept in scalar registers
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int64_t uni64(int64_t v) {
   const int lo = __builtin_amdgcn_readfirstlane(static_cast<int>(v & 0xffffffff));
   const int hi = __builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32));
-  return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
-}
-
-__device__ __forceinline__ int64_t lane64(int64_t v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(v & 0xffffffff), lane);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), lane);
   return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
 }
 
@@ -213,8 +218,26 @@ __device__ __forceinline__ void store_part(GMEM float* q, const float* v) {
   }
 }
 
-// A gather run in LDS (see GatherRun): chunk c of a queue is bags [bs + (c - chunk_base)
-// cb, + cb) of batch slice j of k of its table, clipped to the slice at the runtime batch.
+// The same through a descriptor of the pooled row, which drops what lies past its end (the
+// lanes of a row narrower than its sub-wavefront): a store without a branch.
+constexpr int kNonTemporal = 2;
+template <int P>
+__device__ __forceinline__ void buffer_store_part(i32x4 rsrc, int off, const float* v) {
+  if constexpr (P >= 4) {
+#pragma unroll
+    for (int i = 0; i < P; i += 4)
+      buffer_store_f32x4(f32x4{v[i], v[i + 1], v[i + 2], v[i + 3]}, rsrc, off + 4 * i, 0, kNonTemporal);
+  } else if constexpr (P == 2) {
+    buffer_store_f32x2(f32x2{v[0], v[1]}, rsrc, off, 0, kNonTemporal);
+  } else {
+    static_assert(P == 1, "part size");
+    buffer_store_f32(v[0], rsrc, off, 0, kNonTemporal);
+  }
+}
+
+// A gather run in LDS (see GatherRun; its j and k hold the slice's first and end bag at the
+// runtime batch there): chunk c of a queue is bags [bs + (c - chunk_base) cb, + cb) of the
+// slice, clipped to it.
 struct Chunk {
   int run;      // record in the worker's LDS slot, -1 = none
   int bs, be;   // bags
@@ -224,7 +247,7 @@ struct Chunk {
 // chunk v, then further chunks in order from a counter in LDS.
 struct WaveQueue {
   const LMEM GatherRun* r;
-  int e, e_end, nchunks, B;
+  int e, e_end, nchunks;
   LMEM int* ctr;
   int first;    // this wavefront's first chunk, -1 once taken
   int waves;    // wavefronts of the worker
@@ -243,15 +266,19 @@ struct WaveQueue {
     while (true) {
       const int c = claim();
       if (c >= nchunks) return Chunk{-1, 0, 0};
-      while (e + 1 < e_end && __builtin_amdgcn_readfirstlane(r[e + 1].chunk_base) <= c) ++e;
-      const int j = __builtin_amdgcn_readfirstlane(r[e].j), k = __builtin_amdgcn_readfirstlane(r[e].k);
+      // the run holding chunk c: chunk_base ascends, so count the runs after e that start at or before c
+      while (true) {
+        const int x = e + 1 + static_cast<int>(threadIdx.x & 63);
+        const int passed = __popcll(__ballot(x < e_end && r[min(x, e_end - 1)].chunk_base <= c));
+        e = uni(e + passed);
+        if (passed < 64) break;
+      }
+      const int bs = __builtin_amdgcn_readfirstlane(r[e].j), be = __builtin_amdgcn_readfirstlane(r[e].k);
       const int cb = __builtin_amdgcn_readfirstlane(r[e].cb);
       const int c0b = __builtin_amdgcn_readfirstlane(r[e].chunk_base);
-      const int bs = static_cast<int>((static_cast<int64_t>(j) * B) / k);
-      const int be = static_cast<int>((static_cast<int64_t>(j + 1) * B) / k);
       const int c0 = bs + (c - c0b) * cb;
       const int c1 = min(be, c0 + cb);
-      if (c0 < c1) return Chunk{e, c0, c1};
+      if (c0 < c1) return Chunk{uni(e), uni(c0), uni(c1)};
     }
   }
 };
@@ -299,18 +326,45 @@ __device__ __forceinline__ i32x4 load_row(const RunInfo& ri, int row, int lane_c
   return buffer_load_row(ri.rsrc, row, lane_c, 0, 0);
 }
 
-// kSteps rows, one per instruction u, row id broadcast from lane u of this lane's row of 16
-__device__ __forceinline__ void issue_rows(const RunInfo& ri, int row, int lane_c, int R, i32x4 (&raw)[kSteps]) {
-  if (ri.big()) {
-    GMEM const char* const wb = ri.base() + lane_c;
-    static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
-      raw[u] = *reinterpret_cast<GMEM const i32x4*>(
-          wb + static_cast<uint64_t>(static_cast<uint32_t>(row_bcast<decltype(u)::value>(row))) *
-                   static_cast<uint32_t>(R));
-    });
-  } else {
-    static_for<kSteps>([&](auto u) __attribute__((always_inline)) { raw[u] = buffer_load_row(ri.rsrc, row_bcast<decltype(u)::value>(row), lane_c, 0, 0); });
+// registers that hold nothing (so that what an earlier step left in them is not kept)
+template <int U>
+__device__ __forceinline__ void undefined_rows(i32x4 (&raw)[kSteps]) {
+  if constexpr (U < kSteps) {
+    asm volatile("" : "=v"(raw[U]));
+    undefined_rows<U + 1>(raw);
   }
+}
+
+// The rows of instructions [0, kSteps) that hold some of a step's n lookups, four
+// instructions at a time (the others keep what they held); row id broadcast from lane u of
+// this lane's row of 16.  A row id of `rows` (a lookup past n, an invalid id) reads zeros
+// through the descriptor, with no access to memory.
+template <int S, int U = 0>
+__device__ __forceinline__ void issue_rows(const RunInfo& ri, int row, int lane_c, int n, i32x4 (&raw)[kSteps]) {
+  if constexpr (U < kSteps) {
+    if (U > 0 && U % 4 == 0 && n <= U * S) {
+      undefined_rows<U>(raw);
+    } else {
+      raw[U] = buffer_load_row(ri.rsrc, row_bcast<U>(row), lane_c, 0, 0);
+      issue_rows<S, U + 1>(ri, row, lane_c, n, raw);
+    }
+  }
+}
+// The same for a table past the descriptor's 32-bit offsets (invalid ids read row 0, their
+// values are cleared by clear_rows).
+__device__ __forceinline__ void issue_rows_big(const RunInfo& ri, int row, int lane_c, int R, i32x4 (&raw)[kSteps]) {
+  GMEM const char* const wb = ri.base() + lane_c;
+  static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
+    raw[u] = *reinterpret_cast<GMEM const i32x4*>(
+        wb + static_cast<uint64_t>(static_cast<uint32_t>(row_bcast<decltype(u)::value>(row))) *
+                 static_cast<uint32_t>(R));
+  });
+}
+__device__ __forceinline__ void clear_rows(bool ok, i32x4 (&raw)[kSteps]) {
+  const int okv = ok ? 1 : 0;
+  static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
+    if (!row_bcast<decltype(u)::value>(okv)) raw[u] = zero4();
+  });
 }
 
 // Lane constants of a walker.
@@ -335,198 +389,223 @@ __device__ __forceinline__ LaneConst lane_const(int R) {
 
 // ---------------------------------------------------------------- multi-lookup bags
 
+// The bags of a chunk are summed in 32-bit positions relative to `base`, the chunk's first
+// lookup (a chunk of 2^30 lookups or more is rebased on the way), and per instruction of a
+// step the scalar unit compares the current bag's end with a constant.  Control is scalar
+// throughout -- lanes are masked by selects and dropped stores, and gather.hip is built so
+// that uniform branches stay branches -- which leaves a move, a compare and a jump beside
+// the additions.  Against 64-bit ends and masked branches (512-byte rows, bags of 20: 7.9
+// VALU and 7.5 SALU instructions per lookup, now 4.2 and 4.7): 131M lookups 3751 -> 3605 us,
+// 1.9M weighted lookups 86.5 -> 79.7 us; 256-byte fp16 rows in bags of 8, 119.4 -> 108.7 us;
+// 384-byte rows in bags of 35, 39.6 -> 33.5 us; 1-KB rows in bags of 3, 34.9 -> 19.7 us.
 template <int G, bool F16, bool W>
 struct Multi {
   static constexpr int S = 64 / G;
   static constexpr int NA = F16 ? 8 : 4;
+  static constexpr int P = NA / S;
   static constexpr int N = S * kSteps;   // lookups per step
+  static constexpr int kFar = 1 << 30;   // longest stretch of lookups between rebases
 
-  int lane, sw, lane_sw, lane_c, pos_l;
-  bool active, loads, counts;
-  int R;
-  int64_t ostride;
+  int sw, lane, lane_c, pos_l;
+  int loff;                     // this lane's byte offset in a pooled row
+  int row_out;                  // bytes of a pooled row
+  bool loads, counts;
+  int64_t obytes;               // bytes between a bag's pooled row and the next one's
+
+  // the chunk being summed: bags [b, be), lookups [base + q, base + qend)
+  RunInfo ri;
+  int64_t base, bstart;         // position of q = 0; where bag b starts
+  int q, qend, b, be, wb;
+  int e;                        // end of bag b, relative to base
+  int wrel;                     // lane i: end of bag wb + i, relative to base
+  GMEM char* optr;              // bag b's pooled row
+  Acc<F16> acc;
 
   __device__ __forceinline__ void init(const LookupArgs& a) {
     const LaneConst l = lane_const<G>(a.R);
-    lane = l.lane;
     sw = l.sw;
-    lane_sw = l.lane_sw;
+    lane = l.lane;
     lane_c = l.lane_c;
     pos_l = l.pos_l;
-    active = l.active;
+    loff = (NA * l.lane_sw + P * l.sw) * 4;
+    row_out = a.E * 4;
     loads = l.loads;
     counts = l.counts;
-    R = a.R;
-    ostride = static_cast<int64_t>(a.T) * a.E;
+    obytes = static_cast<int64_t>(a.T) * a.E * 4;
   }
 
-  // ids (and weights) of lookups p + pos_l, those below pend
-  __device__ __forceinline__ void load_ids(const LookupArgs& a, int64_t p, int64_t pend, int64_t& id, float& wt) const {
-    const bool ok = loads && p + pos_l < pend;
-#if EMBX_NT_IDS
-    // a step's ids fill whole lines that no other step or wavefront reads
-    id = ok ? __builtin_nontemporal_load(as_global(a.indices) + p + pos_l) : int64_t(-1);
-    if constexpr (W) wt = ok ? __builtin_nontemporal_load(as_global(a.weights) + p + pos_l) : 0.0f;
-#else
-    id = ok ? as_global(a.indices)[p + pos_l] : int64_t(-1);
-    if constexpr (W) wt = ok ? as_global(a.weights)[p + pos_l] : 0.0f;
-#endif
+  static __device__ __forceinline__ int stretch(int64_t d) { return (d >> 30) != 0 ? kFar : static_cast<int>(d); }
+
+  // a position relative to base, as far as 32 bits go
+  __device__ __forceinline__ int rel32(int64_t pos) const {
+    const int64_t d = pos - base;
+    return (d >> 31) != 0 ? INT32_MAX : static_cast<int>(d);
   }
 
-  __device__ void walk(const LookupArgs& a, const LMEM GatherRun* runs, WaveQueue& q) {
+  // ids (and weights) of the n lookups from `first` on, one per lane at pos_l (n > 0; lanes
+  // past the end read the last one)
+  __device__ __forceinline__ void load_ids(const LookupArgs& a, int64_t first, int n, int64_t& id, float& wt) const {
+    const uint32_t x = static_cast<uint32_t>(min(pos_l, n - 1));
+    id = *reinterpret_cast<GMEM const int64_t*>(reinterpret_cast<GMEM const char*>(as_global(a.indices) + first) + x * 8u);
+    if constexpr (W)
+      wt = *reinterpret_cast<GMEM const float*>(reinterpret_cast<GMEM const char*>(as_global(a.weights) + first) + x * 4u);
+  }
+
+  __device__ void walk(const LookupArgs& a, const LMEM GatherRun* runs, WaveQueue& qu) {
     const CMEM int64_t* const coff = (const CMEM int64_t*)a.offsets;
-    Chunk cur = q.next();
-    if (cur.run < 0) return;
-    RunInfo ri = run_info(runs, cur.run, a);
-    // the chunk's head (scalar loads): first and end positions, end of its first bag
-    int64_t p = coff[static_cast<int64_t>(ri.table) * a.B + cur.bs];
-    int64_t pend = coff[static_cast<int64_t>(ri.table) * a.B + cur.be];
-    int64_t e = coff[static_cast<int64_t>(ri.table) * a.B + cur.bs + 1];
-    // win: ends of bags wb + 1 + lane (vector), for the steps' bag ends
-    int wb = cur.bs;
-    int64_t win = as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(cur.bs + 1 + lane, cur.be)];
-    // the next chunk's head, loaded while this one is walked (its descriptor is formed
-    // again from the run record at the switch)
-    Chunk nxt = q.next();
-    int64_t np = 0, npend = 0, ne = 0;
-    if (nxt.run >= 0) {
-      const int64_t tb = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(runs[nxt.run].table)) * a.B;
-      np = coff[tb + nxt.bs];
-      npend = coff[tb + nxt.be];
-      ne = coff[tb + nxt.bs + 1];
-    }
-    int64_t id;
+    // a chunk's head: where its lookups start and end (scalar loads) and, lane i, where bag
+    // bs + i ends (a chunk holds at most 64 bags)
+    Chunk nxt;
+    int64_t np = 0, npend = 0, nwin = 0;
+    auto fetch = [&]() __attribute__((always_inline)) {
+      nxt = qu.next();
+      if (nxt.run >= 0) {
+        const int64_t tb = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(runs[nxt.run].table)) * a.B;
+        np = uni64(coff[tb + nxt.bs]);
+        npend = uni64(coff[tb + nxt.be]);
+        nwin = as_global(a.offsets)[tb + min(nxt.bs + 1 + lane, nxt.be)];
+      }
+    };
+    int64_t pend;
+    auto open = [&]() __attribute__((always_inline)) {   // the fetched chunk becomes the current one
+      ri = run_info(runs, nxt.run, a);
+      base = np;
+      pend = npend;
+      bstart = np;
+      q = 0;
+      qend = stretch(npend - np);
+      wb = b = nxt.bs;
+      be = nxt.be;
+      wrel = rel32(nwin);
+      e = __builtin_amdgcn_readlane(wrel, 0);
+      optr = reinterpret_cast<GMEM char*>(as_global(a.out) + static_cast<int64_t>(ri.table) * a.E) + b * obytes;
+    };
+    fetch();
+    if (nxt.run < 0) return;
+    open();
+    int64_t id = 0;
     float wt = 0.0f;
-    load_ids(a, p, pend, id, wt);
-    Acc<F16> acc;
+    if (qend > 0) load_ids(a, base, min(N, qend), id, wt);
+    int ahead = 0;   // 1: the chunk after this one has been looked up (nxt)
     acc_zero(acc);
-    int b = cur.bs, be = cur.be;
-    int64_t bstart = p;
-    wait_all();
     while (true) {
-      // ---- chunk cur: bags [b, be), positions [p, pend); ids of [p, p + N) in `id`
-      bool ids_ready = false;   // the first ids of the next chunk are in flight
-      while (p < pend) {
-        const int n = static_cast<int>(min(static_cast<int64_t>(N), pend - p));
+      int ids_ready = 0;   // the first ids of the next chunk are in flight
+      while (true) {
+        if (q >= qend) {
+          if (qend < kFar || base + q >= pend) break;
+          rebase(a, pend, id, wt);   // (a chunk of more than 2^30 lookups)
+        }
+        const int n = uni(min(N, qend - q));
         const bool okp = loads && pos_l < n;
         const bool ok = okp && static_cast<uint64_t>(id) < ri.rows();
-        const int row = ok ? static_cast<int>(id) : 0;
         const uint64_t badm = __ballot(okp && !ok && counts);
         float wl = 0.0f;
         if constexpr (W) wl = ok ? wt : 0.0f;
         i32x4 raw[kSteps];
-        issue_rows(ri, row, lane_c, R, raw);
-        // ids of the next step: more of this chunk, or the start of the next one
-        const int64_t pn = p + n;
-        if (pn < pend) {
-          load_ids(a, pn, pend, id, wt);
-        } else if (nxt.run >= 0) {
-          load_ids(a, np, npend, id, wt);
-          ids_ready = true;
+        if (!ri.big()) {
+          issue_rows<S>(ri, ok ? static_cast<int>(id) : ri.rsrc.z, lane_c, n, raw);
+        } else {
+          issue_rows_big(ri, ok ? static_cast<int>(id) : 0, lane_c, a.R, raw);
         }
-        // ends of the next 64 bags when the window runs short
-        const bool slide = b - wb >= 32;
-        if (slide) win = as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)];
-        wait_all();   // the one wait of the step
-        if (slide) wb = b;
+        // the next chunk's head, two steps before this one ends
+        const int left = uni(qend - q - n);
+        if (uni(ahead) == 0 && left <= N) {
+          fetch();
+          ahead = 1;
+        }
+        // ids of the next step: more of this chunk, or the start of the next one
+        if (left > 0) {
+          load_ids(a, base + (q + n), min(N, left), id, wt);
+        } else if (uni(nxt.run) >= 0 && uni(qend) < kFar && npend > np) {
+          load_ids(a, np, min(N, stretch(npend - np)), id, wt);
+          ids_ready = 1;
+        }
+        asm volatile("" ::: "memory");   // every load of the step is issued before its first use
         if (badm != 0) {   // an out-of-range id is counted and adds nothing
           if (lane == 0) atomicAdd(as_global(a.err), static_cast<unsigned long long>(__popcll(badm)));
         }
-        if (__ballot(okp && !ok) != 0) {
-          const int okv = ok ? 1 : 0;
-          static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
-            if (!row_bcast<decltype(u)::value>(okv)) raw[u] = zero4();
-          });
-        }
-        // additions in lookup order per SW; bag ends are wave-uniform
-        const int wlb = __float_as_int(wl);
-        static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
-          constexpr int U = decltype(u)::value;
-          add_instr(a, acc, raw[U], W ? __int_as_float(row_bcast<U>(wlb)) : a.one, p + U * S, pn, ri, b, be, e,
-                    bstart, wb, win);
-        });
-        p = pn;
+        if (ri.big() && __ballot(loads && !ok) != 0) clear_rows(ok, raw);
+        consume<0>(a, raw, n, __float_as_int(wl));
+        q = uni(q + n);
       }
       // bags left at the chunk's end: one whose last lookup closed the final step (its
       // sum is in acc), then empty ones
-      while (b < be) {
-        finish(a, acc, ri, b, pend - bstart);
-        bstart = pend;
-        ++b;
+      while (uni(b) < uni(be)) {
+        finish(q);
+        b = uni(b + 1);
       }
-      // ---- next chunk
-      if (nxt.run < 0) return;
-      cur = nxt;
-      ri = run_info(runs, cur.run, a);
-      p = np;
-      pend = npend;
-      e = ne;
-      wb = cur.bs;
-      b = cur.bs;
-      be = cur.be;
-      bstart = p;
-      win = as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(cur.bs + 1 + lane, cur.be)];
-      nxt = q.next();
-      if (nxt.run >= 0) {
-        const int64_t tb = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(runs[nxt.run].table)) * a.B;
-        np = coff[tb + nxt.bs];
-        npend = coff[tb + nxt.be];
-        ne = coff[tb + nxt.bs + 1];
-      }
-      if (!ids_ready) {
-        load_ids(a, p, pend, id, wt);
-        wait_all();
-      }
+      if (uni(ahead) == 0) fetch();
+      ahead = 0;
+      if (uni(nxt.run) < 0) break;
+      open();
+      if (uni(ids_ready) == 0 && uni(qend) > 0) load_ids(a, base, min(N, qend), id, wt);
     }
   }
 
-  // Instruction u of a step: lookups qpos + s, one per SW s (those below pn).  Bags
-  // ending inside it split its SWs: SWs before the end add to the ending bag, the others
-  // to the next one.
-  __device__ __forceinline__ void add_instr(const LookupArgs& a, Acc<F16>& acc, const i32x4 x, float w, int64_t qpos,
-                                            int64_t pn, const RunInfo& ri, int& b, int be, int64_t& e,
-                                            int64_t& bstart, int& wb, int64_t& win) const {
-    if (qpos >= pn) return;
-    if (e >= qpos + S) {
+  // moves base to the lookups reached so far, of which more than kFar follow (or followed)
+  __device__ __forceinline__ void rebase(const LookupArgs& a, int64_t pend, int64_t& id, float& wt) {
+    base = uni64(base + q);
+    q = 0;
+    qend = uni(stretch(pend - base));
+    wb = b;
+    wrel = rel32(as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)]);
+    e = b < be ? __builtin_amdgcn_readlane(wrel, 0) : INT32_MAX;
+    load_ids(a, base, min(N, qend), id, wt);
+  }
+
+  // Adds the n lookups of a step: instruction U holds lookups U S + s, one per SW s.  A bag
+  // that ends inside an instruction splits its SWs: those before the end add to the ending
+  // bag, the others to the next one.  (Lookups past n were loaded as zeros, or not loaded.)
+  // Lanes are masked by selects and dropped stores, never by branches: with scalar control
+  // alone the compiler keeps one copy of the sums and of the scalar state.
+  template <int U>
+  __device__ __forceinline__ void consume(const LookupArgs& a, const i32x4 (&raw)[kSteps], int n, int wlb) {
+    if constexpr (U < kSteps) {
+      if (U > 0 && U % 4 == 0 && n <= U * S) return;
+      const float w = W ? __int_as_float(row_bcast<U>(wlb)) : a.one;
+      int r = uni(e - q);
+      asm volatile("" : "+s"(r));   // one compare per instruction (no chains of jumps between them)
+      if (__builtin_expect(r >= (U + 1) * S, 1)) {
+        acc_add(acc, raw[U], w);
+      } else {
+        int lo = 0;
+        do {
+          const int k = r - U * S;
+          if (k > lo) add_only(raw[U], w, sw >= lo && sw < k);
+          finish(e);
+          b = uni(b + 1);
+          lo = k;
+          e = uni(b < be ? __builtin_amdgcn_readlane(wrel, b - wb) : INT32_MAX);
+          r = uni(e - q);
+        } while (r < (U + 1) * S);
+        add_only(raw[U], w, sw >= lo);
+      }
+      consume<U + 1>(a, raw, n, wlb);
+    }
+  }
+  // the lanes' lookups are added where `on` (elsewhere a zero with weight zero: neither an
+  // infinity nor a NaN of another bag's row or weight gets in)
+  __device__ __forceinline__ void add_only(const i32x4 x, float w, bool on) {
+    if constexpr (S == 1) {   // (an end never falls inside an instruction)
       acc_add(acc, x, w);
-      return;
+    } else {
+      acc_add(acc, i32x4{on ? x.x : 0, on ? x.y : 0, on ? x.z : 0, on ? x.w : 0}, W ? (on ? w : 0.0f) : w);
     }
-    int lo = 0;
-    while (e < qpos + S) {
-      const int k = static_cast<int>(e - qpos);
-      if (sw >= lo && sw < k) acc_add(acc, x, w);
-      finish(a, acc, ri, b, e - bstart);
-      ++b;
-      bstart = e;
-      lo = k;
-      if (b >= be) {
-        e = kNoEnd;
-        return;
-      }
-      if (b - wb >= 64) {   // more bag ends in this step than the window holds
-        wb = b;
-        win = as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)];
-        wait_all();
-      }
-      e = lane64(win, b - wb);
-    }
-    if (sw >= lo) acc_add(acc, x, w);
   }
 
-  // bag b is complete in acc (len lookups): combine the SWs, scale a mean, store, clear
-  __device__ __forceinline__ void finish(const LookupArgs& a, Acc<F16>& acc, const RunInfo& ri, int b,
-                                         int64_t len) const {
+  // bag b ends at base + end and is complete in acc: combine the SWs, scale a mean, store, clear
+  __device__ __forceinline__ void finish(int end) {
     reduce_scatter<S, NA>(acc.v);
-    constexpr int P = NA / S;
-    if (ri.mean() && len > 1) {
-      const float s = 1.0f / static_cast<float>(len);
+    const int64_t stop = base + end;
+    if (ri.mean() && uni64(stop - bstart) > 1) {
+      const float s = 1.0f / static_cast<float>(stop - bstart);
 #pragma unroll
       for (int i = 0; i < P; ++i) acc.v[i] *= s;
     }
-    if (active)
-      store_part<P>(as_global(a.out) + static_cast<int64_t>(ri.table) * a.E + static_cast<int64_t>(b) * ostride +
-                        NA * lane_sw + P * sw,
-                    acc.v);
+    bstart = uni64(stop);
+    const uint64_t o = reinterpret_cast<uint64_t>(optr);
+    buffer_store_part<P>(i32x4{static_cast<int>(o), static_cast<int>(o >> 32), row_out, 0x00020000}, loff, acc.v);
+    optr = reinterpret_cast<GMEM char*>(uni64(reinterpret_cast<int64_t>(optr) + obytes));
     acc_zero(acc);
   }
 };
@@ -542,23 +621,24 @@ struct Single {
   static constexpr int NA = F16 ? 8 : 4;
   static constexpr int N = S * kSteps;   // bags per step (= per chunk)
 
-  int lane, sw, lane_sw, lane_c, pos_l;
+  int lane, sw, lane_c, pos_l;
+  uint32_t loff;                // byte offset of this lane's piece of its SW's pooled row
   bool active, loads, counts;
   int R;
-  int64_t ostride;
+  int64_t obytes;               // bytes between a bag's pooled row and the next one's
 
   __device__ __forceinline__ void init(const LookupArgs& a) {
     const LaneConst l = lane_const<G>(a.R);
     lane = l.lane;
     sw = l.sw;
-    lane_sw = l.lane_sw;
     lane_c = l.lane_c;
     pos_l = l.pos_l;
     active = l.active;
     loads = l.loads;
     counts = l.counts;
     R = a.R;
-    ostride = static_cast<int64_t>(a.T) * a.E;
+    obytes = static_cast<int64_t>(a.T) * a.E * 4;
+    loff = static_cast<uint32_t>(l.sw) * static_cast<uint32_t>(obytes) + static_cast<uint32_t>(NA * l.lane_sw) * 4u;
   }
 
   // first and end position of this lane's bag of chunk c (vector loads)
@@ -597,12 +677,14 @@ struct Single {
       // ---- chunk c0: its id has landed; chunk c1's head has landed
       const bool ok = has0 && static_cast<uint64_t>(id0) < r0.rows();
       const uint64_t badm = __ballot(has0 && !ok && counts);
-      const int row = ok ? static_cast<int>(id0) : 0;
-      const int okv = ok ? 1 : 0;
       float wl = 0.0f;
       if constexpr (W) wl = ok ? w0 : 0.0f;
       i32x4 raw[kSteps];
-      issue_rows(r0, row, lane_c, R, raw);
+      const int nb = c0.be - c0.bs;
+      if (!r0.big())
+        issue_rows<S>(r0, ok ? static_cast<int>(id0) : r0.rsrc.z, lane_c, nb, raw);
+      else
+        issue_rows_big(r0, ok ? static_cast<int>(id0) : 0, lane_c, R, raw);
       bool inb1 = false, has1 = false, multi1 = false;
       int64_t id1 = -1;
       float w1 = 0.0f;
@@ -623,17 +705,11 @@ struct Single {
       }
       wait_all();   // the one wait of the step
       if (badm != 0 && lane == 0) atomicAdd(as_global(a.err), static_cast<unsigned long long>(__popcll(badm)));
+      if (r0.big() && __ballot(loads && !ok) != 0) clear_rows(ok, raw);
       // each SW stores its bag's row (zeros for an empty bag or an out-of-range id)
-      const int nb = c0.be - c0.bs;
-      GMEM float* const ob = as_global(a.out) + static_cast<int64_t>(r0.table) * a.E + NA * lane_sw;
-      const int wlb = __float_as_int(wl);
-      static_for<kSteps>([&](auto u) __attribute__((always_inline)) {
-        constexpr int U = decltype(u)::value;
-        const int bi = U * S + sw;
-        const i32x4 x = row_bcast<U>(okv) ? raw[U] : zero4();
-        const float wx = W ? __int_as_float(row_bcast<U>(wlb)) : a.one;
-        if (bi < nb && active) store_row(ob + static_cast<int64_t>(c0.bs + bi) * ostride, x, wx);
-      });
+      GMEM char* const ob = reinterpret_cast<GMEM char*>(as_global(a.out) + static_cast<int64_t>(r0.table) * a.E) +
+                            c0.bs * obytes;
+      store_rows<0>(a, ob, nb, raw, __float_as_int(wl));
       if (__ballot(multi0) != 0) single_slow<G, F16, W>(a, r0, c0.bs, c0.be);
       if (c1.run < 0) return;
       c0 = c1;
@@ -644,6 +720,18 @@ struct Single {
       w0 = w1;
       c1 = c2;
       r1 = r2;
+    }
+  }
+
+  // instruction U's bags U S + s (SW s), those of the chunk's nb
+  template <int U>
+  __device__ __forceinline__ void store_rows(const LookupArgs& a, GMEM char* ob, int nb, const i32x4 (&raw)[kSteps],
+                                             int wlb) const {
+    if constexpr (U < kSteps) {
+      if (U > 0 && U % 4 == 0 && nb <= U * S) return;
+      const float w = W ? __int_as_float(row_bcast<U>(wlb)) : a.one;
+      if (U * S + sw < nb && active) store_row(reinterpret_cast<GMEM float*>(ob + loff), raw[U], w);
+      store_rows<U + 1>(a, ob + S * obytes, nb, raw, wlb);
     }
   }
 
@@ -722,8 +810,17 @@ __global__ void __launch_bounds__(kBlock) EMBX_OCCUPANCY gather_kernel(LookupArg
   if (tw && tid == 0) tw[0] = __builtin_amdgcn_s_memrealtime();
   {   // the worker's slot: a header record, then its runs
     GMEM const char* src = reinterpret_cast<GMEM const char*>(as_global(a.gr) + static_cast<int64_t>(wg) * a.gr_slot);
-    for (int q = tid; q < 3 * a.gr_slot; q += kBlock)
-      *reinterpret_cast<LMEM uint4*>(lds + 16 * q) = *reinterpret_cast<GMEM const uint4*>(src + 16 * q);
+    for (int q = tid; q < 3 * a.gr_slot; q += kBlock) {
+      uint4 x = *reinterpret_cast<GMEM const uint4*>(src + 16 * q);
+      if (q >= 3 && q % 3 == 1) {   // (table, j, k, cb) of a run: slice j of k as bags [floor(jB / k), floor((j+1)B / k))
+        const double B = a.B, j = static_cast<double>(x.y), k = static_cast<double>(x.z);
+        // exact: j B < 2^47, and a quotient below an integer is below it by 1/k >= 2^-16, far
+        // more than the division's rounding
+        x.y = static_cast<uint32_t>(j * B / k);
+        x.z = static_cast<uint32_t>((j + 1.0) * B / k);
+      }
+      *reinterpret_cast<LMEM uint4*>(lds + 16 * q) = x;
+    }
   }
   constexpr int waves = kBlock >> 6;   // (a compile-time count: read from blockDim it costs ~35 VGPRs)
   if (tid == 0) {
@@ -740,7 +837,7 @@ __global__ void __launch_bounds__(kBlock) EMBX_OCCUPANCY gather_kernel(LookupArg
   const LMEM GatherRun* runs = reinterpret_cast<const LMEM GatherRun*>(lds + sizeof(GatherRun));
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (n_single > 0) {
-    WaveQueue q{runs, 0, n_single, single_chunks, a.B, (LMEM int*)&s_ctr[0], wave, waves};
+    WaveQueue q{runs, 0, n_single, single_chunks, (LMEM int*)&s_ctr[0], wave, waves};
     Single<G, F16, W> w;
     w.init(a);
     w.walk(a, runs, q);
@@ -750,7 +847,7 @@ __global__ void __launch_bounds__(kBlock) EMBX_OCCUPANCY gather_kernel(LookupArg
     // last, so that the others start on this queue at once (a permutation of [0, waves):
     // every chunk below `waves` is still some wavefront's first)
     const int busy = n_single > 0 ? min(single_chunks, waves) : 0;
-    WaveQueue q{runs, n_single, nr, multi_chunks, a.B, (LMEM int*)&s_ctr[1], (wave + waves - busy) % waves, waves};
+    WaveQueue q{runs, n_single, nr, multi_chunks, (LMEM int*)&s_ctr[1], (wave + waves - busy) % waves, waves};
     Multi<G, F16, W> w;
     w.init(a);
     w.walk(a, runs, q);

@@ -1,0 +1,89 @@
+"""Where bags end inside the steps of the wave-uniform gather kernel: lengths around one
+instruction (4, 2 or 1 lookups), around the groups of four instructions that a short step
+skips, and around a whole step; runs of empty bags; the most bags a chunk takes; and rows and
+weights that are infinite or NaN, which belong to their own bag only.  Integer tables,
+bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import pool as OP
+
+from gpu_helpers import host_tables, log, to_device, upload_tables
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(64, "f32"), (96, "f32"), (256, "f32"), (128, "f16"), (192, "f16"), (200, "f32")]
+
+
+def length_patterns(g):
+    """Bag lengths of one table: every remainder around the kernel's units."""
+    yield np.arange(0, 70)                                            # every length up to a step and past it
+    yield np.array([16, 15, 17, 32, 31, 33, 48, 47, 49, 64, 63, 65, 128, 127, 129, 1, 0, 0, 0, 1] * 3)
+    yield (g.random(200) < 0.2).astype(np.int64)                      # mostly empty, several ends per instruction
+    yield np.concatenate([np.zeros(70, np.int64), [900], np.zeros(70, np.int64), [1]])
+    yield g.integers(0, 4, size=333)
+
+
+def plan_and_batch(E, dtype, seed, rows, stated_pooling):
+    import paper_2507_01676_amd as embx
+    g = np.random.default_rng(seed)
+    lens = list(length_patterns(g))
+    B = max(len(x) for x in lens)
+    lens = [np.concatenate([x, np.zeros(B - len(x), np.int64)]) for x in lens]
+    T = len(lens)
+    c = W.Config(170, "bag ends", E, dtype, -1.0, 1.0, B, [W.TableSpec(m, "fixed", 1, 1, 1, "uniform") for m in rows])
+    c.value_seeds = [W.value_seed(170, t) for t in range(T)]
+    off = np.zeros(T * B + 1, np.int64)
+    np.cumsum(np.concatenate(lens), out=off[1:])
+    idx = np.concatenate([g.integers(0, m, size=int(x.sum())) for m, x in zip(rows, lens)])
+    stats = [{"mean_pooling": stated_pooling or max(0.1, float(x.mean())), "max_pooling": 0} for x in lens]
+    plan = embx.Plan(rows, E, dtype, stats, B)
+    assert plan.info()["kernel"] == "gather_kernel"
+    return c, plan, W.Batch(B, T, idx, off), g
+
+
+@pytest.mark.parametrize("stated_pooling", [0.0, 1.0, 40.0])   # (chunks of a few bags up to the most)
+@pytest.mark.parametrize("E,dtype", SHAPES)
+def test_every_bag_end_is_found(E, dtype, stated_pooling):
+    import torch
+    log(f"bag ends, E{E} {dtype}, stated pooling {stated_pooling}")
+    rows = [7, 50_000, 300, 9, 2_000]
+    c, plan, batch, g = plan_and_batch(E, dtype, 5, rows, stated_pooling)
+    batch.indices[g.random(batch.indices.size) < 0.02] = -1           # out of range: adds nothing, is counted
+    hw = host_tables(c, W.VAL_INTEGER)
+    plan.bind(upload_tables(hw))
+    idx, off = to_device(batch)
+    psw = g.integers(-3, 4, size=batch.indices.size).astype(np.float32)
+    for w in (None, psw):
+        out = torch.full((batch.B, batch.T, E), float("nan"), device="cuda")
+        plan.lookup(idx, off, batch.B, out, weights=None if w is None else torch.from_numpy(w).cuda())
+        torch.cuda.synchronize()
+        ref, _, bad = OP.pool_reference(hw, batch.indices, batch.offsets, batch.B, psw=w)
+        assert np.array_equal(out.cpu().numpy(), ref)
+        assert plan.check_errors() == bad
+
+
+@pytest.mark.parametrize("E,dtype", SHAPES)
+def test_infinities_and_nans_stay_in_their_bag(E, dtype):
+    import torch
+    log(f"non-finite rows and weights, E{E} {dtype}")
+    rows = [40, 50, 60, 70, 80]
+    c, plan, batch, g = plan_and_batch(E, dtype, 6, rows, 0.0)
+    hw = host_tables(c, W.VAL_INTEGER)
+    for t, w in enumerate(hw):
+        w[3, :] = np.inf
+        w[5, ::2] = np.nan
+        w[8, 1::2] = -np.inf
+    plan.bind(upload_tables(hw))
+    idx, off = to_device(batch)
+    psw = g.integers(1, 4, size=batch.indices.size).astype(np.float32)
+    psw[g.random(psw.size) < 0.02] = np.inf
+    psw[g.random(psw.size) < 0.02] = np.nan
+    with np.errstate(invalid="ignore"):
+        for w in (None, psw):
+            out = torch.full((batch.B, batch.T, E), 7.5, device="cuda")
+            plan.lookup(idx, off, batch.B, out, weights=None if w is None else torch.from_numpy(w).cuda())
+            torch.cuda.synchronize()
+            ref, _, _ = OP.pool_reference(hw, batch.indices, batch.offsets, batch.B, psw=w)
+            assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
