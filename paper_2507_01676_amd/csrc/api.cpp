@@ -489,25 +489,37 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
   // 119.1 us; workload 2, single-lookup bags only, 5.30 / 5.36 / 5.51 us.
   // EMBX_GATHER_STEPS = 12, 13 or 16 overrides it.
   int ksteps = 12;
-  // Bags per chunk of worker w's multi-lookup items for steps of N lookups (item_cb); at most
-  // 64, the bag ends a wavefront holds.
+  // Bags per chunk of worker w's multi-lookup items for steps of N lookups (item_cb): as many
+  // lookups as each wavefront's share of what is left of the queue, so that a queue shorter
+  // than 16 full chunks still occupies all 16 wavefronts and a longer one ends in small
+  // chunks; not below half a step (or the share of the whole queue), where a chunk's start
+  // costs more than it evens out, nor above the cap described above; at most 64 bags, the bag
+  // ends a wavefront holds.  Measured against the cap alone: 60k lookups of 1-KB rows (15 per
+  // wavefront) 19.5 -> 12.6 us, 72k lookups of 384-byte rows 34.2 -> 33.6 us, 3.4M lookups of
+  // 256-byte rows 108.9 -> 107.5 us; half or twice the share: within 2% of it.
   std::vector<int32_t> item_cb(items.size(), 1);
   auto multi_lookup = [&](const DevItem& d) { return d.strat == S_GATHER && stats[d.table].max_pooling != 1; };
   auto bag_lookups = [&](const DevItem& d) { return std::max(1.0, stats[d.table].mean_pooling); };
+  auto slice_lookups = [&](const DevItem& d) {
+    const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+    return static_cast<double>(nb) * bag_lookups(d);
+  };
   auto wave_chunks = [&](int w, double N) {
     const int nwaves = block / 64;
     double W = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
+      if (multi_lookup(items[i])) W += slice_lookups(items[i]);
+    const double cap = std::max(2.0 * N, W / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
+    const double least = std::min(0.5 * N, W / nwaves);
+    double left = W;
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
       const DevItem& d = items[i];
       if (!multi_lookup(d)) continue;
-      const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
-      W += static_cast<double>(nb) * bag_lookups(d);
+      const double target = wave_chunk_override > 0.0 ? wave_chunk_override
+                                                      : std::min(cap, std::max(least, left / nwaves));
+      item_cb[i] = static_cast<int32_t>(std::min(64.0, std::max(1.0, std::floor(target / bag_lookups(d)))));
+      left -= slice_lookups(d);
     }
-    const double target = wave_chunk_override > 0.0 ? wave_chunk_override
-                                                    : std::max(2.0 * N, W / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
-    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
-      if (multi_lookup(items[i]))
-        item_cb[i] = static_cast<int32_t>(std::min(64.0, std::max(1.0, std::floor(target / bag_lookups(items[i])))));
   };
   if (wave_gather) {
     const char* env_steps = std::getenv("EMBX_GATHER_STEPS");
