@@ -19,10 +19,10 @@ ARCH = "gfx950"
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract=off",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-I", os.path.join(ROOT, "include")]
-# gather.hip's control flow is wave-uniform: leave it as written instead of turning every branch
+# For kernels whose control flow is wave-uniform: leave it as written instead of turning every branch
 # into the flag-guarded form that divergent branches need (a compare, a jump and the additions per
 # instruction of a step, against about twenty instructions)
-GATHER_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
+UNIFORM_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-Wall"]
 
 
@@ -44,8 +44,10 @@ def _run(cmd, verbose):
 
 
 # lookup.hip is compiled in parts (EMBX_PART): one per (row type, weighted) kernel
-# family, plus the probes, filler and launch code
-LOOKUP_PARTS = 5
+# family, plus the probes, filler and launch code, plus one per family of gather-only
+# kernels with wave-uniform control
+LOOKUP_PARTS = 9
+LOOKUP_UNIFORM_PARTS = (5, 6, 7, 8)
 # gather.hip: one part per (row type, weighted) kernel family, each built for every number
 # of row loads in flight per step a plan may choose (kGatherStepChoices in device_types.hpp)
 GATHER_PARTS = 4
@@ -75,12 +77,13 @@ def build(verbose: bool = False) -> str:
     cmds, objs = [], []
     for part in range(LOOKUP_PARTS):
         o = os.path.join(BUILD, f"lookup_{part}.o")
-        cmds.append([hipcc, *HIP_FLAGS, f"-DEMBX_PART={part}", "-c", os.path.join(CSRC, "lookup.hip"), "-o", o])
+        uniform = UNIFORM_FLAGS if part in LOOKUP_UNIFORM_PARTS else []
+        cmds.append([hipcc, *HIP_FLAGS, *uniform, f"-DEMBX_PART={part}", "-c", os.path.join(CSRC, "lookup.hip"), "-o", o])
         objs.append(o)
     for ks in GATHER_STEPS:
         for part in range(GATHER_PARTS):
             o = os.path.join(BUILD, f"gather_{part}_k{ks}.o")
-            cmds.append([hipcc, *HIP_FLAGS, *GATHER_FLAGS, f"-DEMBX_GPART={part}", f"-DEMBX_GKS={ks}", "-c",
+            cmds.append([hipcc, *HIP_FLAGS, *UNIFORM_FLAGS, f"-DEMBX_GPART={part}", f"-DEMBX_GKS={ks}", "-c",
                          os.path.join(CSRC, "gather.hip"), "-o", o])
             objs.append(o)
     o = os.path.join(BUILD, "api.o")

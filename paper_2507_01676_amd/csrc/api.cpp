@@ -521,6 +521,21 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
       left -= slice_lookups(d);
     }
   };
+  // The same for the rows that lookup_kernel walks in matrix slots, whose chunks are S = 64 / G SWs
+  // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue.
+  auto narrow_chunks = [&](int w) {
+    const int S = 64 / p->G, M = std::min(4, static_cast<int>(p->G)), nwaves = block / 64;
+    double left = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
+      if (multi_lookup(items[i])) left += slice_lookups(items[i]);
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      const DevItem& d = items[i];
+      if (!multi_lookup(d)) continue;
+      const double m = std::floor(left / (nwaves * S * bag_lookups(d)));
+      item_cb[i] = S * static_cast<int32_t>(std::min(static_cast<double>(M), std::max(1.0, m)));
+      left -= slice_lookups(d);
+    }
+  };
   if (wave_gather) {
     const char* env_steps = std::getenv("EMBX_GATHER_STEPS");
     if (env_steps && *env_steps) {
@@ -597,6 +612,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
       // (the SWs then work on fewer tables at a time), hence the cap
       const double target = std::min(128.0, std::max(8.0, std::floor(std::sqrt(5.0 * Ws / nsw))));
       if (wave_gather) wave_chunks(w, static_cast<double>(ksteps) * (64 / p->G));
+      else if (uses_slots(p->G, p->f16)) narrow_chunks(w);
       const double wtarget = std::min(wave_chunk, std::max(1.0, std::floor(Ww / nwaves)));
       gr_ptr[w] = static_cast<int32_t>(gr.size());
       int64_t base[3] = {0, 0, 0};
@@ -607,7 +623,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
           if (d.strat != S_GATHER || class_of(d) != cls) continue;
           const double s_t = std::max(1.0, stats[d.table].mean_pooling);
           const int32_t cb = cls == 1 ? (wave_gather ? ksteps * (64 / p->G) : kChunkSingle)
-                             : cls == 2 && wave_gather ? item_cb[i]
+                             : cls == 2 && (wave_gather || uses_slots(p->G, p->f16)) ? item_cb[i]
                                       : static_cast<int32_t>(std::max(1.0, std::floor((cls == 0 ? wtarget : target) / s_t)));
           const int64_t nc = (slice_bags_any(d) + cb - 1) / cb;
           if (nc == 0) continue;

@@ -61,6 +61,12 @@ static_assert(sizeof(GatherSlotHeader) == sizeof(GatherRun), "a slot header take
 constexpr int kStaticLdsReserve = 1024;   // LDS kept for the kernel's static variables
 constexpr int kChunkSingle = 8;           // bags per chunk of a single-lookup-bag run (one SW step)
 
+// Whether lookup_kernel's multi-lookup gather queue is walked by wavefronts in matrix slots (for
+// rows of G lanes), else by sub-wavefronts.  Not for one lane (nothing to share) nor for 8
+// lanes of fp16, where the conversions cost what the slots save (bags of 4: 26.0 against
+// 26.3 us, bags of 30: 79 against 74 us).
+constexpr bool uses_slots(int G, bool f16) { return G == 2 || G == 4 || (G == 8 && !f16); }
+
 struct LookupArgs {
   const DevItem* items;
   const int32_t* wg_ptr;        // [K + 1] item ranges per worker

@@ -30,7 +30,7 @@
 //          three queues of small chunks: long bags (wave mode), bags of at most
 //          one lookup (a chunk of kU bags is one SW step and each row is its
 //          bag's output), and the rest (SW mode, walked as one stream across
-//          chunks).  Invalid ids read a row of zeros; fp16 halves are added with
+//          chunks; narrow rows by wavefronts in matrix slots, see Slots).  Invalid ids read a row of zeros; fp16 halves are added with
 //          a mixed-precision fma.
 //
 // All pointers carry their address space (1 = global, 3 = LDS) so that every
@@ -40,14 +40,16 @@
 
 #include <algorithm>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "device_types.hpp"
 
 // The lookup kernels are compiled in parts so that a build can run the parts in
 // parallel: EMBX_PART 0..3 holds the kernels of one (row type, weighted) pair, part 4
-// the probes, the table filler and the launch code.  Without EMBX_PART one compile
-// holds everything.
+// the probes, the table filler and the launch code, parts 5..8 the pair's kernels of
+// gather-only plans with rows in matrix slots (their control is wave-uniform, see
+// build.py).  Without EMBX_PART one compile holds everything.
 #ifndef EMBX_PART
 #define EMBX_PART -1
 #endif
@@ -327,6 +329,41 @@ struct FDedup : RowBase {
   __device__ __forceinline__ uint4 take(int32_t, int32_t, const Raw& r) const { return r; }
 };
 
+// a value that is the same in every lane, kept in scalar registers
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// lane U of this lane's SW of G <= 8 lanes by DPP lane moves (no LDS round trip): quad
+// permutes, or row_newbcast to the lower and the upper half of each row of 16
+template <int G, int U>
+__device__ __forceinline__ int sw_bcast(int v) {
+  static_assert(G <= 8 && U < G, "one row of 16 lanes holds whole SWs");
+  if constexpr (G == 1) return v;
+  else if constexpr (G == 2) return __builtin_amdgcn_mov_dpp(v, (U | U << 2 | (2 + U) << 4 | (2 + U) << 6), 0xF, 0xF, true);
+  else if constexpr (G == 4) return __builtin_amdgcn_mov_dpp(v, U * 0x55, 0xF, 0xF, true);
+  else {
+    const int lo = __builtin_amdgcn_mov_dpp(v, 0x150 + U, 0xF, 0xF, true);
+    return __builtin_amdgcn_update_dpp(lo, v, 0x158 + U, 0xF, 0xC, false);
+  }
+}
+// The same for the SW walkers, of any G.  They are bound by the vector unit, so from 8 lanes
+// on, where DPP takes two instructions, they shuffle through LDS (0.26M bags of 4 lookups of
+// 128-byte fp16 rows: 323 us, 348 with DPP).
+template <int G, int U>
+__device__ __forceinline__ int sw_share(int v) {
+  if constexpr (G <= 4) return sw_bcast<G, U>(v);
+  else return __shfl(v, U, G);
+}
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// f(integral_constant 0), ..., f(integral_constant N - 1): DPP controls are immediates
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 // The kU upcoming lookups of a SW are loaded one per lane (IPL per lane when the SW
 // has fewer than kU lanes): position u sits in lane u % G, slot u / G.  Positions past
 // the end read `safe` (a valid position) and are marked invalid; validity is applied
@@ -368,8 +405,7 @@ struct Ids {
       mine[j] = (in_range && ok) ? static_cast<int32_t>(raw[j]) : -1;
       if (in_range && !ok) f.bad();
     }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) ix[u] = G == 1 ? mine[u] : __shfl(mine[u / G], u % G, G);
+    static_for<kU>([&](auto u) __attribute__((always_inline)) { ix[u] = sw_share<G, u % G>(mine[u / G]); });
   }
 
   // The row address of each of the kU lookups, for this lane's 16 bytes of the row:
@@ -385,24 +421,19 @@ struct Ids {
       if (in_range && !ok) f.bad();
       mine[j] = reinterpret_cast<int64_t>(in_range && ok ? f.w + raw[j] * f.R : f.zero);
     }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      int64_t v = mine[u / G];
-      if constexpr (G > 1) {
-        const int lo = __shfl(static_cast<int>(v & 0xffffffff), u % G, G);
-        const int hi = __shfl(static_cast<int>(v >> 32), u % G, G);
-        v = (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
-      }
-      a[u] = reinterpret_cast<gchar*>(v) + f.lane_c;
-    }
+    static_for<kU>([&](auto u) __attribute__((always_inline)) {
+      const int64_t v = mine[u / G];
+      const int lo = sw_share<G, u % G>(static_cast<int>(v & 0xffffffff));
+      const int hi = sw_share<G, u % G>(static_cast<int>(v >> 32));
+      a[u] = reinterpret_cast<gchar*>((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo)) + f.lane_c;
+    });
   }
 
   // the weight of each of the kU lookups (the run-time 1 without weights)
   __device__ __forceinline__ void weights(const RowBase& f, float (&wt)[kU]) const {
     float mine[W ? IPL : 1];
     own_weights(f, mine);
-#pragma unroll
-    for (int u = 0; u < kU; ++u) wt[u] = weight_of(f, mine, u);
+    static_for<kU>([&](auto u) __attribute__((always_inline)) { wt[u] = weight_of<u>(f, mine); });
   }
   // the weights of this lane's own positions (0 past the end or for an invalid id) ...
   __device__ __forceinline__ void own_weights(const RowBase& f, float (&mine)[W ? IPL : 1]) const {
@@ -416,9 +447,10 @@ struct Ids {
     }
   }
   // ... and position u's weight, shared within the SW when it is used
-  static __device__ __forceinline__ float weight_of(const RowBase& f, const float (&mine)[W ? IPL : 1], int u) {
+  template <int U>
+  static __device__ __forceinline__ float weight_of(const RowBase& f, const float (&mine)[W ? IPL : 1]) {
     if constexpr (!W) return f.one;
-    else return G == 1 ? mine[u] : __shfl(mine[u / G], u % G, G);
+    else return __int_as_float(sw_share<G, U % G>(__float_as_int(mine[U / G])));
   }
 };
 
@@ -1258,8 +1290,7 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
       // (a lane outside the row stores nothing and keeps no output pointer: its bag
       // count b follows from m alone)
       const uint32_t fs = f.active ? fm : 0u;
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {   // lookups past the end read the zero row
+      static_for<kU>([&](auto u) __attribute__((always_inline)) {   // lookups past the end read the zero row
         if ((fs >> u) & 1u) {
           if (mean) acc_mean(acc, p + u - bstart);
           bstart = p + u;
@@ -1267,14 +1298,13 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
           acc_zero(acc);
           obb += ostride;
         }
-        acc_add(acc, raw[u], Ids<G, W>::weight_of(f, wm, u));
-      }
+        acc_add(acc, raw[u], Ids<G, W>::template weight_of<u>(f, wm));
+      });
       b += m;
     } else {
       wait_all();
       int64_t e = off[min(b + 1, be)];   // end of bag b
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
+      static_for<kU>([&](auto u) __attribute__((always_inline)) {
         while (u < n && e == p + u) {
           if (mean) acc_mean(acc, e - bstart);
           bstart = e;
@@ -1284,8 +1314,8 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
           obb += ostride;
           e = off[min(b + 1, be)];
         }
-        acc_add(acc, raw[u], Ids<G, W>::weight_of(f, wm, u));
-      }
+        acc_add(acc, raw[u], Ids<G, W>::template weight_of<u>(f, wm));
+      });
       win = off[min(b + 1 + lane_sw, be)];
       wait_all();
     }
@@ -1421,14 +1451,15 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
       multi = multi || h0.en[j] - h0.st[j] > 1;
     }
     uint4 raw[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t a = G == 1 ? addr[u] : lane_i64_sw(addr[u / G], u % G, G);
-      raw[u] = ldg16(reinterpret_cast<gchar*>(a) + f.lane_c);
-    }
+    static_for<kU>([&](auto u) __attribute__((always_inline)) {
+      const int lo = sw_share<G, u % G>(static_cast<int>(addr[u / G] & 0xffffffff));
+      const int hi = sw_share<G, u % G>(static_cast<int>(addr[u / G] >> 32));
+      raw[u] = ldg16(reinterpret_cast<gchar*>((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo)) + f.lane_c);
+    });
     float wt[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) wt[u] = !W ? 0.0f : G == 1 ? wm[u] : __shfl(wm[u / G], u % G, G);
+    static_for<kU>([&](auto u) __attribute__((always_inline)) {
+      wt[u] = W ? __int_as_float(sw_share<G, u % G>(__float_as_int(wm[u / G]))) : 0.0f;
+    });
     wait_all();   // the one wait of the step
     const int nb = cur.be - cur.bs;
 #pragma unroll
@@ -1467,6 +1498,254 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
   }
 }
 
+// ---------------------------------------------------------------- gather: narrow rows in matrix slots
+//
+// Rows of 32 to 128 bytes (uses_slots).  A wavefront takes a chunk of bags of one table,
+// M = min(4, G) slots per SW: SW s of the S = 64 / G sums m' <= M consecutive bags, so the S
+// SWs walk S streams of lookups side by side and a row load covers S rows through one
+// descriptor.  v_mfma_f32_4x4x1 does the sums: it multiplies 16 blocks of 4 lanes, each D[4][4]
+// += A[4] B[4], with B a block's piece of the rows and A[m] = 1 (or the weight) where the
+// lookup belongs to bag m of the SW, else 0.  So a lookup costs its loads, two instructions
+// for A and NA matrix instructions for S rows, and bag ends cost nothing inside a step: no
+// branch, no masked store, no copy of the sums.  Each step of D is an fma in lookup order
+// (bit for bit the sum the other walkers make).  A zero times an infinity or NaN would put a
+// NaN into the SW's other bags, so a chunk with any non-finite sum is summed again bag by bag.
+// G < 4: a block holds 4 / G SWs, and a lane uses the part of D whose slots are its own SW's.
+//
+// What bounds it: the 128-byte lines beyond L2 (57 G/s on this device at any row size) on
+// large batches, the chain of offsets, ids and rows on small ones.  Before, each SW walked its
+// own stream of one table, with addresses shared by LDS shuffles and a masked store per
+// lookup: 68 vector instructions per row load, here 11 and 4 matrix instructions (fp32).  Bags
+// of 8 of 64-byte rows: 1.6M lookups 25.0 -> 18.1 us, 13.6M 156 -> 142 us; 128-byte rows 34.1
+// -> 25.2 us, bags of 20 59.2 -> 48.8 us, of 60 128 -> 122 us, of 2 23.0 -> 14.4 us.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+}  // namespace
+// structured buffer load of 16 bytes: base + vindex * stride + voffset, zeros where vindex >= num_records
+__device__ i32x4 narrow_buffer_load(i32x4 rsrc, int vindex, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.struct.buffer.load.v4i32");
+namespace {
+
+// slot U's value (lanes U, U + M, ... of the SW hold slot U's)
+template <int G, int U>
+__device__ __forceinline__ int slot_bcast(int v) {
+  return sw_bcast<(G < 4 ? G : 4), U>(v);
+}
+template <int G, int U>
+__device__ __forceinline__ int64_t slot_bcast64(int64_t v) {
+  const int lo = slot_bcast<G, U>(static_cast<int>(v & 0xffffffff)), hi = slot_bcast<G, U>(static_cast<int>(v >> 32));
+  return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
+}
+
+template <int G, bool F16, bool W>
+struct Slots {
+  static constexpr int S = kWave / G, M = G < 4 ? G : 4;
+  static constexpr int NA = F16 ? 8 : 4;
+  static constexpr int kUS = 8;               // rows in flight per SW (16 spill registers)
+  static constexpr int IPL = kUS / G;         // ids per lane of a step: lane c holds lookups c, c + G, ...
+
+  struct Chunk {   // bags [c0, c1) of run `run` (-1: none), and this lane's slot of it
+    int run, c0, c1, mp;
+    int64_t st, en;
+  };
+
+  const LookupArgs& a;
+  const LMEM GatherRun* runs;
+  int e, e_end, nchunks, first;
+  LMEM int* ctr;
+  int lane, sw, slot;
+
+  __device__ __forceinline__ void claim(Chunk& c) {
+    while (true) {
+      int x = first;
+      first = -1;
+      if (x < 0) {
+        if (lane == 0) x = atomicAdd(ctr, 1);
+        x = __builtin_amdgcn_readfirstlane(x);
+      }
+      if (x >= nchunks) {
+        c.run = -1;
+        return;
+      }
+      while (true) {   // the run holding chunk x: chunk_base ascends
+        const int y = e + 1 + lane;
+        const int passed = __popcll(__ballot(y < e_end && runs[min(y, e_end - 1)].chunk_base <= x));
+        e = __builtin_amdgcn_readfirstlane(e + passed);
+        if (passed < kWave) break;
+      }
+      const LMEM GatherRun& r = runs[e];
+      // floor(j B / k) exactly: j B < 2^47, and a quotient below an integer is below it by 1/k >= 2^-16
+      const double B = a.B, j = r.j, k = r.k;
+      const int cb = __builtin_amdgcn_readfirstlane(r.cb);
+      const int bs = __builtin_amdgcn_readfirstlane(static_cast<int>(j * B / k));
+      const int be = __builtin_amdgcn_readfirstlane(static_cast<int>((j + 1.0) * B / k));
+      c.c0 = uni(bs + (x - uni(r.chunk_base)) * cb);
+      c.c1 = uni(min(be, c.c0 + cb));
+      if (c.c0 < c.c1) {
+        c.run = uni(e);
+        c.mp = uni((c.c1 - c.c0 + S - 1) / S);
+        const int64_t tb = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(r.table)) * a.B;
+        const int b0 = c.c0 + sw * c.mp + min(slot, c.mp), b1 = c.c0 + sw * c.mp + min(slot + 1, c.mp);
+        c.st = as_global(a.offsets)[tb + min(b0, c.c1)];
+        c.en = as_global(a.offsets)[tb + min(b1, c.c1)];
+        return;
+      }
+    }
+  }
+
+  // ids (and weights) of lookups p + c + G j of this SW, those below pend (else -1)
+  __device__ __forceinline__ void load_ids(int64_t p, int64_t pend, int lane_sw, int64_t (&id)[IPL], float (&wt)[IPL]) const {
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+      const int64_t pos = p + lane_sw + j * G;
+      const bool ok = pos < pend;
+      id[j] = ok ? as_global(a.indices)[pos] : int64_t(-1);
+      if constexpr (W) wt[j] = ok ? as_global(a.weights)[pos] : 0.0f;
+    }
+  }
+
+  __device__ __forceinline__ void walk(const Lane& l, const RowBase& rb0) {
+    Chunk cur, nxt;
+    claim(cur);
+    if (uni(cur.run) < 0) return;
+    claim(nxt);
+    int64_t p = slot_bcast64<G, 0>(cur.st), pend = slot_bcast64<G, M - 1>(cur.en);
+    int64_t id[IPL];
+    float wt[IPL];
+    load_ids(p, pend, l.lane_sw, id, wt);
+    const int64_t ost = static_cast<int64_t>(a.T) * a.E;
+    while (true) {
+      const LMEM GatherRun& g = runs[uni(cur.run)];
+      const uint64_t wb = reinterpret_cast<uint64_t>(g.w);
+      const uint32_t rows = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(g.rows)));
+      i32x4 rsrc;
+      rsrc.x = __builtin_amdgcn_readfirstlane(static_cast<int>(wb & 0xffffffffu));
+      rsrc.y = __builtin_amdgcn_readfirstlane(static_cast<int>(((wb >> 32) & 0xffffu) | (static_cast<uint32_t>(a.R) << 16)));
+      rsrc.z = static_cast<int>(rows);
+      rsrc.w = 0x00020000;
+      const int table = __builtin_amdgcn_readfirstlane(g.table);
+      const bool mean = __builtin_amdgcn_readfirstlane(g.mean) != 0;
+      // (the descriptor's offsets are 32 bits wide)
+      const bool big = static_cast<uint64_t>(rows) * static_cast<uint64_t>(a.R) >= (uint64_t(1) << 32);
+      f32x4 d[NA];
+#pragma unroll
+      for (int i = 0; i < NA; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      int64_t np = 0, npend = 0;
+      while (true) {
+        int row[IPL];
+        float wl[IPL];
+#pragma unroll
+        for (int j = 0; j < IPL; ++j) {
+          const bool in = p + l.lane_sw + j * G < pend;
+          const bool ok = static_cast<uint64_t>(id[j]) < rows;
+          if (in && !ok) atomicAdd(as_global(a.err), 1ull);
+          row[j] = ok ? static_cast<int>(id[j]) : big ? -1 : static_cast<int>(rows);
+          wl[j] = W && ok ? wt[j] : 0.0f;
+        }
+        i32x4 raw[kUS];
+        if (!big) {
+          static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+            raw[u] = narrow_buffer_load(rsrc, sw_bcast<G, u % G>(row[u / G]), rb0.lane_c, 0, 0);
+          });
+        } else {
+          static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+            const int r = sw_bcast<G, u % G>(row[u / G]);
+            raw[u] = *reinterpret_cast<GMEM const i32x4*>(
+                (r >= 0 ? as_global(static_cast<const char*>(g.w)) + static_cast<int64_t>(r) * a.R : rb0.zero) + rb0.lane_c);
+          });
+        }
+        // this lane's slot in the step: lookups [rs, re)
+        const int rs = static_cast<int>(max(int64_t(0), min64(cur.st - p, kUS)));
+        const int re = static_cast<int>(max(int64_t(0), min64(cur.en - p, kUS)));
+        const uint32_t in_slot = ((1u << re) - 1u) & ~((1u << rs) - 1u);
+        p += kUS;
+        const bool more = __ballot(p < pend) != 0;
+        if (more) {
+          load_ids(p, pend, l.lane_sw, id, wt);
+        } else if (nxt.run >= 0) {   // the first ids of the next chunk
+          np = slot_bcast64<G, 0>(nxt.st);
+          npend = slot_bcast64<G, M - 1>(nxt.en);
+          load_ids(np, npend, l.lane_sw, id, wt);
+        }
+        asm volatile("" ::: "memory");   // every load of the step is issued before its first use
+        static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+          const int one = W ? sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0])) : 0x3f800000;
+          const float f = __int_as_float(__builtin_amdgcn_sbfe(static_cast<int>(in_slot), u, 1) & one);
+          const i32x4 x = raw[u];
+          if constexpr (!F16) {
+            d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
+            d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
+            d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
+            d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
+          } else {
+            const int h[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const uint32_t v = static_cast<uint32_t>(h[i]);
+              d[2 * i] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+                  f, __half2float(__ushort_as_half(static_cast<unsigned short>(v & 0xffffu))), d[2 * i], 0, 0, 0);
+              d[2 * i + 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+                  f, __half2float(__ushort_as_half(static_cast<unsigned short>(v >> 16))), d[2 * i + 1], 0, 0, 0);
+            }
+          }
+        });
+        if (!more) break;
+      }
+      // ---- store the chunk's bags: register r of d holds slot r (G < 4: of the block)
+      float t = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t = __builtin_fmaf(d[i][r], 0.0f, t);
+      GMEM float* const ob = as_global(a.out) + static_cast<int64_t>(table) * a.E + l.lane_sw * NA;
+      if (__ballot(!(t == 0.0f)) == 0) {
+        float scale = 1.0f;
+        if (mean && cur.en - cur.st > 1) scale = 1.0f / static_cast<float>(cur.en - cur.st);
+        const int hi = G < 4 ? (lane & 3) / G * G : 0;   // first register of this lane's SW
+        static_for<M>([&](auto r) __attribute__((always_inline)) {
+          constexpr int rr = decltype(r)::value;
+          Acc<F16> acc;
+#pragma unroll
+          for (int i = 0; i < NA; ++i) {
+            float v = d[i][rr];
+            if constexpr (G == 2) v = hi ? d[i][rr + 2] : v;
+            if constexpr (G == 1) v = hi == 0 ? d[i][0] : hi == 1 ? d[i][1] : hi == 2 ? d[i][2] : d[i][3];
+            acc.v[i] = v;
+          }
+          if (mean) {
+            const float sc = __int_as_float(slot_bcast<G, rr>(__float_as_int(scale)));
+#pragma unroll
+            for (int i = 0; i < NA; ++i) acc.v[i] *= sc;
+          }
+          const int b = cur.c0 + sw * cur.mp + rr;
+          if (rr < cur.mp && b < cur.c1 && l.active) acc_store(ob + static_cast<int64_t>(b) * ost, acc);
+        });
+      } else {
+        for (int r = 0; r < cur.mp; ++r) {   // bag by bag (invalid ids have been counted)
+          const int b = cur.c0 + sw * cur.mp + r;
+          if (b >= cur.c1) break;
+          GMEM const int64_t* off = as_global(a.offsets) + static_cast<int64_t>(table) * a.B + b;
+          const int64_t k0 = off[0], k1 = off[1];
+          Acc<F16> acc;
+          acc_zero(acc);
+          for (int64_t k = k0; k < k1; ++k) {
+            const int64_t x = as_global(a.indices)[k];
+            if (static_cast<uint64_t>(x) >= rows) continue;
+            acc_add(acc, ldg16(as_global(static_cast<const char*>(g.w)) + x * a.R + rb0.lane_c),
+                    W ? as_global(a.weights)[k] : rb0.one);
+          }
+          if (mean) acc_mean(acc, k1 - k0);
+          if (l.active) acc_store(ob + static_cast<int64_t>(b) * ost, acc);
+        }
+      }
+      if (uni(nxt.run) < 0) break;
+      cur = nxt;
+      p = np;
+      pend = npend;
+      claim(nxt);
+    }
+  }
+};
+
 // Gather slices.  A worker's gather slices are cut into three queues of chunks (runs
 // of bags of one slice): long-bag slices (wave mode), single-lookup-bag slices, and
 // the rest (SW mode).  Wavefront v takes wave-mode chunks v, v + 16, ... and SW s
@@ -1484,7 +1763,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     for (int q = l.tid; q < 3 * a.gr_slot; q += kBlock) sts16(lds + 16 * q, ldg16(src + 16 * q));
   }
   constexpr int NSW = kBlock / G;
-  if (l.tid == 0) *qctr = NSW;   // the SW-mode queue's counter, after its first round
+  if (l.tid == 0) *qctr = uses_slots(G, F16) ? kNumWaves : NSW;   // the last queue's counter, after its first round
   __syncthreads();
   const LMEM GatherSlotHeader* hd = reinterpret_cast<const LMEM GatherSlotHeader*>(lds);
   const int n_wave = hd->n_wave, wave_chunks = hd->wave_chunks, n_single = hd->n_single,
@@ -1518,7 +1797,12 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     static_cast<RowBase&>(f) = rb0;
     walk_single<G, F16, W>(idx, offsets, out, a.E, a.B, ost, l.lane_sw, f, q);
   }
-  {  // SW mode
+  if constexpr (uses_slots(G, F16)) {   // narrow rows: chunks taken by wavefronts
+    const int lane = l.tid & (kWave - 1);
+    Slots<G, F16, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
+                       lane, l.sw_w, lane & (Slots<G, F16, W>::M - 1)};
+    if (sw_chunks > 0) w.walk(l, rb0);
+  } else {  // SW mode
     RunQueue q{runs, n_wave + n_single, nr, sw_chunks, a.B, true, qctr, l.lane_sw, G, l.sw, NSW};
     FGather f;
     static_cast<RowBase&>(f) = rb0;
@@ -1664,13 +1948,25 @@ __global__ void __launch_bounds__(256) fill_kernel(char* dst, int64_t row_begin,
 
 using KernelFn = void (*)(LookupArgs);
 
+template <int G, bool F16, bool STAGED, bool W>
+KernelFn pick_one() {
+  if constexpr (!STAGED && uses_slots(G, F16)) return nullptr;   // parts 5..8
+  else return &lookup_kernel<G, F16, STAGED, W>;
+}
+template <bool F16, bool W>
+KernelFn pick_slots(int G) {
+  if (G == 2) return &lookup_kernel<2, F16, false, W>;
+  if (G == 4) return &lookup_kernel<4, F16, false, W>;
+  if constexpr (uses_slots(8, F16)) return &lookup_kernel<8, F16, false, W>;
+  return nullptr;
+}
 template <bool F16, bool STAGED, bool W>
 KernelFn pick(int G) {
   switch (G) {
-    case 1: return &lookup_kernel<1, F16, STAGED, W>;
-    case 2: return &lookup_kernel<2, F16, STAGED, W>;
-    case 4: return &lookup_kernel<4, F16, STAGED, W>;
-    case 8: return &lookup_kernel<8, F16, STAGED, W>;
+    case 1: return pick_one<1, F16, STAGED, W>();
+    case 2: return pick_one<2, F16, STAGED, W>();
+    case 4: return pick_one<4, F16, STAGED, W>();
+    case 8: return pick_one<8, F16, STAGED, W>();
     case 16: return &lookup_kernel<16, F16, STAGED, W>;
     case 32: return &lookup_kernel<32, F16, STAGED, W>;
     case 64: return &lookup_kernel<64, F16, STAGED, W>;
@@ -1687,6 +1983,10 @@ LookupKernelFn lookup_kernel_f32(int G, bool staged);
 LookupKernelFn lookup_kernel_f32_weighted(int G, bool staged);
 LookupKernelFn lookup_kernel_f16(int G, bool staged);
 LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged);
+LookupKernelFn slots_kernel_f32(int G);
+LookupKernelFn slots_kernel_f32_weighted(int G);
+LookupKernelFn slots_kernel_f16(int G);
+LookupKernelFn slots_kernel_f16_weighted(int G);
 
 #if EMBX_HAS_PART(0)
 LookupKernelFn lookup_kernel_f32(int G, bool staged) {
@@ -1709,10 +2009,27 @@ LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged) {
 }
 #endif
 
+#if EMBX_HAS_PART(5)
+LookupKernelFn slots_kernel_f32(int G) { return pick_slots<false, false>(G); }
+#endif
+#if EMBX_HAS_PART(6)
+LookupKernelFn slots_kernel_f32_weighted(int G) { return pick_slots<false, true>(G); }
+#endif
+#if EMBX_HAS_PART(7)
+LookupKernelFn slots_kernel_f16(int G) { return pick_slots<true, false>(G); }
+#endif
+#if EMBX_HAS_PART(8)
+LookupKernelFn slots_kernel_f16_weighted(int G) { return pick_slots<true, true>(G); }
+#endif
+
 #if EMBX_HAS_PART(4)
 namespace {
 
 LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted) {
+  if (!staged && uses_slots(G, f16)) {
+    if (f16) return weighted ? slots_kernel_f16_weighted(G) : slots_kernel_f16(G);
+    return weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
+  }
   if (f16) return weighted ? lookup_kernel_f16_weighted(G, staged) : lookup_kernel_f16(G, staged);
   return weighted ? lookup_kernel_f32_weighted(G, staged) : lookup_kernel_f32(G, staged);
 }

@@ -1,8 +1,9 @@
-"""Where bags end inside the steps of the wave-uniform gather kernel: lengths around one
-instruction (4, 2 or 1 lookups), around the groups of four instructions that a short step
-skips, and around a whole step; runs of empty bags; the most bags a chunk takes; and rows and
-weights that are infinite or NaN, which belong to their own bag only.  Integer tables,
-bit-exact against the oracle."""
+"""Where bags end inside the steps of the gather walkers: lengths around one instruction (64 / G
+lookups of G-lane rows), around the groups of four instructions that a short step skips, and
+around a whole step; runs of empty bags; the most bags a chunk takes; rows and weights that
+are infinite or NaN, which belong to their own bag only; and a narrow table past 4 GiB.  Wide
+rows (gather_kernel) and narrow ones (lookup_kernel: in matrix slots, or by sub-wavefronts).
+Integer tables, bit-exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,10 @@ from gpu_helpers import host_tables, log, to_device, upload_tables
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(64, "f32"), (96, "f32"), (256, "f32"), (128, "f16"), (192, "f16"), (200, "f32")]
+WIDE = [(64, "f32"), (96, "f32"), (256, "f32"), (128, "f16"), (192, "f16"), (200, "f32")]
+NARROW = [(4, "f32"), (8, "f32"), (16, "f32"), (24, "f32"), (32, "f32"), (8, "f16"), (16, "f16"), (24, "f16"),
+          (32, "f16"), (64, "f16")]
+SHAPES = WIDE + NARROW
 
 
 def length_patterns(g):
@@ -39,7 +43,7 @@ def plan_and_batch(E, dtype, seed, rows, stated_pooling):
     idx = np.concatenate([g.integers(0, m, size=int(x.sum())) for m, x in zip(rows, lens)])
     stats = [{"mean_pooling": stated_pooling or max(0.1, float(x.mean())), "max_pooling": 0} for x in lens]
     plan = embx.Plan(rows, E, dtype, stats, B)
-    assert plan.info()["kernel"] == "gather_kernel"
+    assert plan.info()["kernel"] == ("gather_kernel" if (E, dtype) in WIDE else "lookup_kernel")
     return c, plan, W.Batch(B, T, idx, off), g
 
 
@@ -87,3 +91,29 @@ def test_infinities_and_nans_stay_in_their_bag(E, dtype):
             torch.cuda.synchronize()
             ref, _, _ = OP.pool_reference(hw, batch.indices, batch.offsets, batch.B, psw=w)
             assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
+
+
+def test_narrow_rows_of_a_table_beyond_4_gib():
+    import torch
+
+    import paper_2507_01676_amd as embx
+    E, rows, B = 16, 70_000_000, 600
+    log(f"one table of {rows * E * 4 / 2**30:.2f} GiB, rows of {E * 4} bytes")
+    w = torch.empty((rows, E), device="cuda")
+    embx.fill_table(w, 0, 99, mode=W.VAL_INTEGER)
+    g = np.random.default_rng(3)
+    lens = g.integers(0, 9, size=B)
+    off = np.zeros(B + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    idx = g.integers(0, rows, size=int(off[-1]))
+    idx[::7] = rows - 1 - idx[::7] % 1000
+    idx[5::50] = rows
+    plan = embx.Plan([rows], E, "f32", [{"mean_pooling": 4.0, "max_pooling": 8}], B).bind([w])
+    d_idx, d_off = to_device(W.Batch(B, 1, idx, off))
+    got = plan.lookup(d_idx, d_off, B).cpu().numpy()
+    ok = idx < rows
+    vals = np.zeros((idx.size, E), np.float32)
+    vals[ok] = W.table_rows_at(0, idx[ok], E, "f32", seed=99, mode=W.VAL_INTEGER)
+    ref, _, _ = OP.pool_reference([vals], np.arange(idx.size, dtype=np.int64), off, B)
+    assert np.array_equal(got, ref)
+    assert plan.check_errors() == int((~ok).sum())
