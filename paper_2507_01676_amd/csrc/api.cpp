@@ -49,6 +49,7 @@ struct emb_plan {
   GatherRun* d_gr = nullptr;
   const char* d_zero_row = nullptr;      // R zero bytes
   bool staged = false;                   // the plan has LDS / HOT / DEDUP / STREAM slices
+  bool slots = false;                    // lookup_kernel sums multi-lookup gather bags in matrix slots
   bool wave_gather = false;              // launches the wave-uniform gather kernel (gather.hip)
   int block = kBlock;                    // threads per worker
   int ksteps = 0;                        // gather_kernel: row loads in flight per lane per step
@@ -521,6 +522,31 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
       left -= slice_lookups(d);
     }
   };
+  // Narrow rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one by
+  // one.  In slots a chunk is bags of one slice, one or more per SW, so the slices must hold
+  // bags for half of a wavefront's S SWs (1.6M lookups in bags of 8, 30 per slice: 18.1 us
+  // against 25.0; bags of 30, 3 per slice of 800 queries: 19.9 against 15.6).  fp16 rows of 4
+  // and 8 lanes also pay conversions: they gain on bags of up to 12 where each SW of the worker
+  // has at least 16 lookups (0.5M lookups in bags of 4: 26.1 against 27.1 us, 4M 313 / 349, 8M in
+  // bags of 8 198 / 206, of 24 360 / 347; 160k in bags of 8, 5 per SW: 12.0 / 11.1) and on bags
+  // of up to 3 (2 at 500 queries: 6.5 / 9.4).
+  if (!wave_gather && !staged && (p->G == 2 || p->G == 4 || p->G == 8)) {
+    const double S = 64.0 / p->G;
+    double bags = 0.0, lookups = 0.0, filled = 0.0;
+    for (const DevItem& d : items)
+      if (multi_lookup(d)) {
+        const double n = slice_lookups(d), nb = n / bag_lookups(d);
+        bags += nb;
+        lookups += n;
+        filled += n * std::min(1.0, nb / S);
+      }
+    p->slots = bags > 0.0 && filled >= 0.5 * lookups;
+    if (p->f16 && p->G >= 4) {
+      const double per_sw = lookups / (static_cast<double>(K) * (block / p->G));
+      p->slots = p->slots && ((lookups <= 3.0 * bags && (per_sw <= 3.0 || per_sw >= 8.0)) ||
+                              (lookups <= 12.0 * bags && per_sw >= 16.0));
+    }
+  }
   // The same for the rows that lookup_kernel walks in matrix slots, whose chunks are S = 64 / G SWs
   // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue.
   auto narrow_chunks = [&](int w) {
@@ -612,7 +638,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
       // (the SWs then work on fewer tables at a time), hence the cap
       const double target = std::min(128.0, std::max(8.0, std::floor(std::sqrt(5.0 * Ws / nsw))));
       if (wave_gather) wave_chunks(w, static_cast<double>(ksteps) * (64 / p->G));
-      else if (uses_slots(p->G, p->f16)) narrow_chunks(w);
+      else if (p->slots) narrow_chunks(w);
       const double wtarget = std::min(wave_chunk, std::max(1.0, std::floor(Ww / nwaves)));
       gr_ptr[w] = static_cast<int32_t>(gr.size());
       int64_t base[3] = {0, 0, 0};
@@ -623,7 +649,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
           if (d.strat != S_GATHER || class_of(d) != cls) continue;
           const double s_t = std::max(1.0, stats[d.table].mean_pooling);
           const int32_t cb = cls == 1 ? (wave_gather ? ksteps * (64 / p->G) : kChunkSingle)
-                             : cls == 2 && (wave_gather || uses_slots(p->G, p->f16)) ? item_cb[i]
+                             : cls == 2 && (wave_gather || p->slots) ? item_cb[i]
                                       : static_cast<int32_t>(std::max(1.0, std::floor((cls == 0 ? wtarget : target) / s_t)));
           const int64_t nc = (slice_bags_any(d) + cb - 1) / cb;
           if (nc == 0) continue;
@@ -903,7 +929,8 @@ emb_status_t lookup_impl(emb_plan_t* plan, const int64_t* indices, const int64_t
   if (plan->wave_gather)
     return st(launch_gather(a, plan->G, plan->f16, weighted, plan->ksteps, plan->K, plan->block, plan->lds_bytes,
                             stream));
-  return st(launch_lookup(a, plan->G, plan->f16, plan->staged, weighted, plan->K, plan->lds_bytes, stream));
+  return st(launch_lookup(a, plan->G, plan->f16, plan->staged, weighted, plan->slots, plan->K, plan->lds_bytes,
+                          stream));
 }
 
 }  // namespace

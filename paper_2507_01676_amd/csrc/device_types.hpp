@@ -61,12 +61,6 @@ static_assert(sizeof(GatherSlotHeader) == sizeof(GatherRun), "a slot header take
 constexpr int kStaticLdsReserve = 1024;   // LDS kept for the kernel's static variables
 constexpr int kChunkSingle = 8;           // bags per chunk of a single-lookup-bag run (one SW step)
 
-// Whether lookup_kernel's multi-lookup gather queue is walked by wavefronts in matrix slots (for
-// rows of G lanes), else by sub-wavefronts.  Not for one lane (nothing to share) nor for 8
-// lanes of fp16, where the conversions cost what the slots save (bags of 4: 26.0 against
-// 26.3 us, bags of 30: 79 against 74 us).
-constexpr bool uses_slots(int G, bool f16) { return G == 2 || G == 4 || (G == 8 && !f16); }
-
 struct LookupArgs {
   const DevItem* items;
   const int32_t* wg_ptr;        // [K + 1] item ranges per worker
@@ -119,9 +113,10 @@ EMBX_DECL_GATHER(13)
 EMBX_DECL_GATHER(16)
 #undef EMBX_DECL_GATHER
 
-// Host-callable launchers (defined in lookup.hip).
-int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, int grid, int lds_bytes,
-                  void* stream);
+// Host-callable launchers (defined in lookup.hip).  slots: the kernel whose multi-lookup gather
+// queue is cut for wavefronts that sum bags in matrix slots (gather-only plans, G 2 to 8).
+int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, bool slots, int grid,
+                  int lds_bytes, void* stream);
 int launch_gather(const LookupArgs& a, int G, bool f16, bool weighted, int ks, int grid, int block, int lds_bytes,
                   void* stream);
 // workgroups of `block` threads of the gather kernels for rows of G lanes that fit on one CU

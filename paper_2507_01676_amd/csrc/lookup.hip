@@ -1500,7 +1500,7 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
 
 // ---------------------------------------------------------------- gather: narrow rows in matrix slots
 //
-// Rows of 32 to 128 bytes (uses_slots).  A wavefront takes a chunk of bags of one table,
+// Rows of 32 to 128 bytes, where the plan says so.  A wavefront takes a chunk of bags of one table,
 // M = min(4, G) slots per SW: SW s of the S = 64 / G sums m' <= M consecutive bags, so the S
 // SWs walk S streams of lookups side by side and a row load covers S rows through one
 // descriptor.  v_mfma_f32_4x4x1 does the sums: it multiplies 16 blocks of 4 lanes, each D[4][4]
@@ -1755,7 +1755,8 @@ struct Slots {
 // tables (cache-resident vs HBM-bound) or from step to step.  The worker's runs are
 // first copied into LDS (`lds`), so that finding a chunk's table and bags costs no
 // memory round trip.
-template <int G, bool F16, bool W>
+// SLOTS: the multi-lookup queue is cut for Slots (chunks per wavefront), not for SWs.
+template <int G, bool F16, bool W, bool SLOTS>
 __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, const Lane& l, int wg,
                                              LMEM int* qctr) {
   {   // the worker's slot: a header record, then its runs
@@ -1763,7 +1764,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     for (int q = l.tid; q < 3 * a.gr_slot; q += kBlock) sts16(lds + 16 * q, ldg16(src + 16 * q));
   }
   constexpr int NSW = kBlock / G;
-  if (l.tid == 0) *qctr = uses_slots(G, F16) ? kNumWaves : NSW;   // the last queue's counter, after its first round
+  if (l.tid == 0) *qctr = SLOTS ? kNumWaves : NSW;   // the last queue's counter, after its first round
   __syncthreads();
   const LMEM GatherSlotHeader* hd = reinterpret_cast<const LMEM GatherSlotHeader*>(lds);
   const int n_wave = hd->n_wave, wave_chunks = hd->wave_chunks, n_single = hd->n_single,
@@ -1797,7 +1798,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     static_cast<RowBase&>(f) = rb0;
     walk_single<G, F16, W>(idx, offsets, out, a.E, a.B, ost, l.lane_sw, f, q);
   }
-  if constexpr (uses_slots(G, F16)) {   // narrow rows: chunks taken by wavefronts
+  if constexpr (SLOTS) {   // narrow rows: chunks taken by wavefronts
     const int lane = l.tid & (kWave - 1);
     Slots<G, F16, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
                        lane, l.sw_w, lane & (Slots<G, F16, W>::M - 1)};
@@ -1812,7 +1813,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
 
 // STAGED = false: the plan has gather slices only (no LDS, no staged-slice code).
 // W: every lookup carries a weight (a.weights).
-template <int G, bool F16, bool STAGED, bool W>
+template <int G, bool F16, bool STAGED, bool W, bool SLOTS>
 __global__ void __launch_bounds__(kBlock) lookup_kernel(LookupArgs a) {
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ int s_last;
@@ -1852,7 +1853,7 @@ __global__ void __launch_bounds__(kBlock) lookup_kernel(LookupArgs a) {
   }
   if (tw && l.tid == 0) tw[1] = now_ticks();
   __syncthreads();   // staged slices are done with LDS
-  gather_phase<G, F16, W>(a, (lchar*)smem_raw, l, wg, (LMEM int*)&s_queue);
+  gather_phase<G, F16, W, SLOTS>(a, (lchar*)smem_raw, l, wg, (LMEM int*)&s_queue);
   if (tw && (l.tid & (kWave - 1)) == 0) tw[2 + l.wave] = now_ticks();
 }
 
@@ -1948,28 +1949,24 @@ __global__ void __launch_bounds__(256) fill_kernel(char* dst, int64_t row_begin,
 
 using KernelFn = void (*)(LookupArgs);
 
-template <int G, bool F16, bool STAGED, bool W>
-KernelFn pick_one() {
-  if constexpr (!STAGED && uses_slots(G, F16)) return nullptr;   // parts 5..8
-  else return &lookup_kernel<G, F16, STAGED, W>;
-}
+// gather-only kernels whose multi-lookup queue is cut for Slots
 template <bool F16, bool W>
 KernelFn pick_slots(int G) {
-  if (G == 2) return &lookup_kernel<2, F16, false, W>;
-  if (G == 4) return &lookup_kernel<4, F16, false, W>;
-  if constexpr (uses_slots(8, F16)) return &lookup_kernel<8, F16, false, W>;
+  if (G == 2) return &lookup_kernel<2, F16, false, W, true>;
+  if (G == 4) return &lookup_kernel<4, F16, false, W, true>;
+  if (G == 8) return &lookup_kernel<8, F16, false, W, true>;
   return nullptr;
 }
 template <bool F16, bool STAGED, bool W>
 KernelFn pick(int G) {
   switch (G) {
-    case 1: return pick_one<1, F16, STAGED, W>();
-    case 2: return pick_one<2, F16, STAGED, W>();
-    case 4: return pick_one<4, F16, STAGED, W>();
-    case 8: return pick_one<8, F16, STAGED, W>();
-    case 16: return &lookup_kernel<16, F16, STAGED, W>;
-    case 32: return &lookup_kernel<32, F16, STAGED, W>;
-    case 64: return &lookup_kernel<64, F16, STAGED, W>;
+    case 1: return &lookup_kernel<1, F16, STAGED, W, false>;
+    case 2: return &lookup_kernel<2, F16, STAGED, W, false>;
+    case 4: return &lookup_kernel<4, F16, STAGED, W, false>;
+    case 8: return &lookup_kernel<8, F16, STAGED, W, false>;
+    case 16: return &lookup_kernel<16, F16, STAGED, W, false>;
+    case 32: return &lookup_kernel<32, F16, STAGED, W, false>;
+    case 64: return &lookup_kernel<64, F16, STAGED, W, false>;
     default: return nullptr;
   }
 }
@@ -2025,8 +2022,8 @@ LookupKernelFn slots_kernel_f16_weighted(int G) { return pick_slots<true, true>(
 #if EMBX_HAS_PART(4)
 namespace {
 
-LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted) {
-  if (!staged && uses_slots(G, f16)) {
+LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted, bool slots) {
+  if (!staged && slots) {
     if (f16) return weighted ? slots_kernel_f16_weighted(G) : slots_kernel_f16(G);
     return weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
   }
@@ -2060,8 +2057,9 @@ int prepare_lookup_kernels(int device, int max_dynamic_lds) {
   std::lock_guard<std::mutex> lock(mu);
   if (static_cast<size_t>(device) < done.size() && done[device]) return 0;
   for (int G = 1; G <= 64; G <<= 1) {
-    for (int f = 0; f < 8; ++f) {
-      LookupKernelFn k = pick_any(G, (f & 1) != 0, (f & 4) == 0, (f & 2) != 0);
+    for (int f = 0; f < 16; ++f) {
+      LookupKernelFn k = pick_any(G, (f & 1) != 0, (f & 4) == 0, (f & 2) != 0, (f & 8) != 0);
+      if (!k) continue;   // (not built in this form)
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                               max_dynamic_lds) != hipSuccess)
         return 4;
@@ -2085,9 +2083,9 @@ int prepare_lookup_kernels(int device, int max_dynamic_lds) {
   return 0;
 }
 
-int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, int grid, int lds_bytes,
-                  void* stream) {
-  LookupKernelFn k = pick_any(G, f16, staged, weighted);
+int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, bool slots, int grid,
+                  int lds_bytes, void* stream) {
+  LookupKernelFn k = pick_any(G, f16, staged, weighted, slots);
   if (!k) return 2;
   hipLaunchKernelGGL(k, dim3(grid), dim3(kBlock), lds_bytes, static_cast<hipStream_t>(stream), a);
   return hipGetLastError() == hipSuccess ? 0 : 4;
