@@ -72,8 +72,14 @@ int next_pow2_log2(int64_t x) {
   return l;
 }
 
+// Lanes of a SW: a power of two that covers a row, at least 2 (of a 16-byte row the second
+// idles).  Alone, a lane would hold all the ids, weights and bag ends that a SW's lanes share:
+// such kernels spilled 300-500 registers, and their scratch costs each launch several us.
+// fp16, one lane against two: 8 tables of 4332 one-lookup bags 10.8 -> 5.0 us, 12 weighted
+// tables at batch 1 24.1 -> 13.4, 8M lookups in bags of 40 75.0 -> 72.3; 1.6M lookups in
+// bags of 8 18.9 -> 20.5 (24.6 before matrix slots), the one shape where one lane led.
 int lanes_per_row(int32_t R) {
-  int g = 1;
+  int g = 2;
   while (g * 16 < R) g <<= 1;
   return g;
 }
