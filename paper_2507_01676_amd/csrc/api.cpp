@@ -72,14 +72,8 @@ int next_pow2_log2(int64_t x) {
   return l;
 }
 
-// Lanes of a SW: a power of two that covers a row, at least 2 (of a 16-byte row the second
-// idles).  Alone, a lane would hold all the ids, weights and bag ends that a SW's lanes share:
-// such kernels spilled 300-500 registers, and their scratch costs each launch several us.
-// fp16, one lane against two: 8 tables of 4332 one-lookup bags 10.8 -> 5.0 us, 12 weighted
-// tables at batch 1 24.1 -> 13.4, 8M lookups in bags of 40 75.0 -> 72.3; 1.6M lookups in
-// bags of 8 18.9 -> 20.5 (24.6 before matrix slots), the one shape where one lane led.
 int lanes_per_row(int32_t R) {
-  int g = 2;
+  int g = 1;
   while (g * 16 < R) g <<= 1;
   return g;
 }
@@ -349,7 +343,14 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
   p->T = num_tables;
   p->E = embedding_dim;
   p->R = P.R;
-  p->G = lanes_per_row(P.R);
+  // Gather-only plans take at least two lanes per row (of a 16-byte row the second idles).
+  // Alone, a lane would hold all the ids, weights and bag ends that a SW's lanes share: such
+  // kernels spilled 300-500 registers, and their scratch costs each launch several us.  One
+  // lane against two: 8 tables of 4332 one-lookup fp16 bags 10.8 -> 5.0 us, 12 weighted tables
+  // at batch 1 24.1 -> 13.4, 8M lookups in bags of 40 75.0 -> 72.3, 49.6 in fp32 (73.3); fp16
+  // bags of 8, 1.6M lookups, 18.9 -> 20.5 (24.6 before matrix slots).  Staged plans keep one
+  // lane: their LDS rows lose more by half the SWs (all-LDS fp32 8.3 -> 9.5 ms, HOT 62 -> 71 us).
+  p->G = gather_only(P) ? std::max(2, lanes_per_row(P.R)) : lanes_per_row(P.R);
   p->K = K;
   p->Bmax = max_batch;
   p->f16 = dtype == EMB_DTYPE_F16;

@@ -337,7 +337,8 @@ __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlan
 template <int G, int U>
 __device__ __forceinline__ int sw_bcast(int v) {
   static_assert(G <= 8 && U < G, "one row of 16 lanes holds whole SWs");
-  if constexpr (G == 2) return __builtin_amdgcn_mov_dpp(v, (U | U << 2 | (2 + U) << 4 | (2 + U) << 6), 0xF, 0xF, true);
+  if constexpr (G == 1) return v;
+  else if constexpr (G == 2) return __builtin_amdgcn_mov_dpp(v, (U | U << 2 | (2 + U) << 4 | (2 + U) << 6), 0xF, 0xF, true);
   else if constexpr (G == 4) return __builtin_amdgcn_mov_dpp(v, U * 0x55, 0xF, 0xF, true);
   else {
     const int lo = __builtin_amdgcn_mov_dpp(v, 0x150 + U, 0xF, 0xF, true);
@@ -1143,7 +1144,7 @@ struct SegHead {
 // mirror the row; wider SWs add shuffles across rows.
 template <int G>
 __device__ __forceinline__ uint32_t sw_or(uint32_t x) {
-  x |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0xB1, 0xF, 0xF, true));
+  if constexpr (G >= 2) x |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0xB1, 0xF, 0xF, true));
   if constexpr (G >= 4) x |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x4E, 0xF, 0xF, true));
   if constexpr (G >= 8) x |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x141, 0xF, 0xF, true));
   if constexpr (G >= 16) x |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x140, 0xF, 0xF, true));
@@ -1467,8 +1468,8 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
     if (__ballot(multi) != 0) {   // bags of more than one lookup: sum them again in lookup order
 #pragma unroll 1
       for (int u = 0; u < kU; ++u) {
-        const int64_t s0 = lane_i64_sw(h0.st[u / G], u % G, G);
-        const int64_t e0 = lane_i64_sw(h0.en[u / G], u % G, G);
+        const int64_t s0 = G == 1 ? h0.st[u] : lane_i64_sw(h0.st[u / G], u % G, G);
+        const int64_t e0 = G == 1 ? h0.en[u] : lane_i64_sw(h0.en[u / G], u % G, G);
         if (u < nb && e0 - s0 > 1) {
           Acc<F16> acc;
           acc_zero(acc);
@@ -1707,6 +1708,7 @@ struct Slots {
           for (int i = 0; i < NA; ++i) {
             float v = d[i][rr];
             if constexpr (G == 2) v = hi ? d[i][rr + 2] : v;
+            if constexpr (G == 1) v = hi == 0 ? d[i][0] : hi == 1 ? d[i][1] : hi == 2 ? d[i][2] : d[i][3];
             acc.v[i] = v;
           }
           if (mean) {
@@ -1958,6 +1960,9 @@ KernelFn pick_slots(int G) {
 template <bool F16, bool STAGED, bool W>
 KernelFn pick(int G) {
   switch (G) {
+    case 1:   // staged plans only
+      if constexpr (STAGED) return &lookup_kernel<1, F16, true, W, false>;
+      return nullptr;
     case 2: return &lookup_kernel<2, F16, STAGED, W, false>;
     case 4: return &lookup_kernel<4, F16, STAGED, W, false>;
     case 8: return &lookup_kernel<8, F16, STAGED, W, false>;
@@ -2053,7 +2058,7 @@ int prepare_lookup_kernels(int device, int max_dynamic_lds) {
   if (device < 0 || max_dynamic_lds < kMetaReserve) return 1;
   std::lock_guard<std::mutex> lock(mu);
   if (static_cast<size_t>(device) < done.size() && done[device]) return 0;
-  for (int G = 2; G <= 64; G <<= 1) {
+  for (int G = 1; G <= 64; G <<= 1) {
     for (int f = 0; f < 16; ++f) {
       LookupKernelFn k = pick_any(G, (f & 1) != 0, (f & 4) == 0, (f & 2) != 0, (f & 8) != 0);
       if (!k) continue;   // (not built in this form)
