@@ -42,6 +42,7 @@
 #include <utility>
 
 #include "device_types.hpp"
+#include "positions.hpp"
 
 #ifndef EMBX_GPART
 #define EMBX_GPART -1
@@ -390,7 +391,7 @@ __device__ __forceinline__ LaneConst lane_const(int R) {
 // ---------------------------------------------------------------- multi-lookup bags
 
 // The bags of a chunk are summed in 32-bit positions relative to `base`, the chunk's first
-// lookup (a chunk of 2^30 lookups or more is rebased on the way), and per instruction of a
+// lookup (a chunk of more than kFar lookups is rebased on the way), and per instruction of a
 // step the scalar unit compares the current bag's end with a constant.  Control is scalar
 // throughout -- lanes are masked by selects and dropped stores, and gather.hip is built so
 // that uniform branches stay branches -- which leaves a move, a compare and a jump beside
@@ -404,7 +405,6 @@ struct Multi {
   static constexpr int NA = F16 ? 8 : 4;
   static constexpr int P = NA / S;
   static constexpr int N = S * kSteps;   // lookups per step
-  static constexpr int kFar = 1 << 30;   // longest stretch of lookups between rebases
 
   int sw, lane, lane_c, pos_l;
   int loff;                     // this lane's byte offset in a pooled row
@@ -432,14 +432,6 @@ struct Multi {
     loads = l.loads;
     counts = l.counts;
     obytes = static_cast<int64_t>(a.T) * a.E * 4;
-  }
-
-  static __device__ __forceinline__ int stretch(int64_t d) { return (d >> 30) != 0 ? kFar : static_cast<int>(d); }
-
-  // a position relative to base, as far as 32 bits go
-  __device__ __forceinline__ int rel32(int64_t pos) const {
-    const int64_t d = pos - base;
-    return (d >> 31) != 0 ? INT32_MAX : static_cast<int>(d);
   }
 
   // ids (and weights) of the n lookups from `first` on, one per lane at pos_l (n > 0; lanes
@@ -476,7 +468,7 @@ struct Multi {
       qend = stretch(npend - np);
       wb = b = nxt.bs;
       be = nxt.be;
-      wrel = rel32(nwin);
+      wrel = rel32(nwin - base);
       e = __builtin_amdgcn_readlane(wrel, 0);
       optr = reinterpret_cast<GMEM char*>(as_global(a.out) + static_cast<int64_t>(ri.table) * a.E) + b * obytes;
     };
@@ -493,7 +485,7 @@ struct Multi {
       while (true) {
         if (q >= qend) {
           if (qend < kFar || base + q >= pend) break;
-          rebase(a, pend, id, wt);   // (a chunk of more than 2^30 lookups)
+          rebase(a, pend, id, wt);   // (a chunk of more than kFar lookups)
         }
         const int n = uni(min(N, qend - q));
         const bool okp = loads && pos_l < n;
@@ -548,7 +540,7 @@ struct Multi {
     q = 0;
     qend = uni(stretch(pend - base));
     wb = b;
-    wrel = rel32(as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)]);
+    wrel = rel32(as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)] - base);
     e = b < be ? __builtin_amdgcn_readlane(wrel, 0) : INT32_MAX;
     load_ids(a, base, min(N, qend), id, wt);
   }
