@@ -14,6 +14,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libembx.so")
+# the same library, except that the 12-load gather kernels rebase their positions after at most
+# FAR lookups instead of 2^30, so that tests reach that code with ordinary batches
+FAR_LIB = os.path.join(HERE, "libembx_far.so")
+FAR = 100
 ARCH = "gfx950"
 
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract=off",
@@ -86,6 +90,12 @@ def build(verbose: bool = False) -> str:
             cmds.append([hipcc, *HIP_FLAGS, *UNIFORM_FLAGS, f"-DEMBX_GPART={part}", f"-DEMBX_GKS={ks}", "-c",
                          os.path.join(CSRC, "gather.hip"), "-o", o])
             objs.append(o)
+    far = {}
+    for part in range(GATHER_PARTS):
+        o = os.path.join(BUILD, f"gather_{part}_k12_far.o")
+        cmds.append([hipcc, *HIP_FLAGS, *UNIFORM_FLAGS, f"-DEMBX_GPART={part}", "-DEMBX_GKS=12", f"-DEMBX_FAR={FAR}",
+                     "-c", os.path.join(CSRC, "gather.hip"), "-o", o])
+        far[os.path.join(BUILD, f"gather_{part}_k12.o")] = o
     o = os.path.join(BUILD, "api.o")
     cmds.append([hipcc, *HIP_FLAGS, "-x", "hip", "-c", os.path.join(CSRC, "api.cpp"), "-o", o])
     objs.append(o)
@@ -94,9 +104,10 @@ def build(verbose: bool = False) -> str:
     cmds.append(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "planner.cpp"), "-o", o])
     objs.append(o)
     _run_all(cmds, verbose)
-    tmp = LIB + ".tmp"
-    _run([hipcc, "-shared", f"--offload-arch={ARCH}", "-o", tmp, *objs], verbose)
-    os.replace(tmp, LIB)
+    for lib, parts in ((FAR_LIB, [far.get(o, o) for o in objs]), (LIB, objs)):
+        tmp = lib + ".tmp"
+        _run([hipcc, "-shared", f"--offload-arch={ARCH}", "-o", tmp, *parts], verbose)
+        os.replace(tmp, lib)
     return LIB
 
 

@@ -405,6 +405,7 @@ struct Multi {
   static constexpr int NA = F16 ? 8 : 4;
   static constexpr int P = NA / S;
   static constexpr int N = S * kSteps;   // lookups per step
+  static constexpr int kFar = far_of(N);   // longest stretch of lookups between rebases
 
   int sw, lane, lane_c, pos_l;
   int loff;                     // this lane's byte offset in a pooled row
@@ -465,7 +466,7 @@ struct Multi {
       pend = npend;
       bstart = np;
       q = 0;
-      qend = stretch(npend - np);
+      qend = stretch(npend - np, kFar);
       wb = b = nxt.bs;
       be = nxt.be;
       wrel = rel32(nwin - base);
@@ -509,7 +510,7 @@ struct Multi {
         if (left > 0) {
           load_ids(a, base + (q + n), min(N, left), id, wt);
         } else if (uni(nxt.run) >= 0 && uni(qend) < kFar && npend > np) {
-          load_ids(a, np, min(N, stretch(npend - np)), id, wt);
+          load_ids(a, np, min(N, stretch(npend - np, kFar)), id, wt);
           ids_ready = 1;
         }
         asm volatile("" ::: "memory");   // every load of the step is issued before its first use
@@ -538,7 +539,7 @@ struct Multi {
   __device__ __forceinline__ void rebase(const LookupArgs& a, int64_t pend, int64_t& id, float& wt) {
     base = uni64(base + q);
     q = 0;
-    qend = uni(stretch(pend - base));
+    qend = uni(stretch(pend - base, kFar));
     wb = b;
     wrel = rel32(as_global(a.offsets)[static_cast<int64_t>(ri.table) * a.B + min(b + 1 + lane, be)] - base);
     e = b < be ? __builtin_amdgcn_readlane(wrel, 0) : INT32_MAX;

@@ -117,3 +117,50 @@ def test_narrow_rows_of_a_table_beyond_4_gib():
     ref, _, _ = OP.pool_reference([vals], np.arange(idx.size, dtype=np.int64), off, B)
     assert np.array_equal(got, ref)
     assert plan.check_errors() == int((~ok).sum())
+
+
+@pytest.mark.parametrize("pooling", ["sum", "mean"])
+@pytest.mark.parametrize("E,dtype", [(64, "f32"), (96, "f32"), (256, "f32"), (128, "f16"), (256, "f16")])
+def test_chunks_longer_than_the_rebase_distance(monkeypatch, E, dtype, pooling):
+    """Positions inside a chunk are 32 bits wide and rebased every 2^30 lookups; in the test
+    build every 96 (100 rounded down to whole steps): bags that end on, beside, a few lookups
+    past and far past such a point."""
+    import importlib.util
+
+    import torch
+
+    import paper_2507_01676_amd as embx
+    log(f"rebased positions, E{E} {dtype} {pooling}")
+    monkeypatch.setenv("EMBX_LIBRARY", embx.LIB_PATH.replace("libembx.so", "libembx_far.so"))
+    monkeypatch.setenv("EMBX_GATHER_STEPS", "12")
+    spec = importlib.util.spec_from_file_location("embx_far", embx.__file__)
+    far = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(far)
+    g = np.random.default_rng(11)
+    lens = [np.concatenate([[95, 1, 1, 96, 97, 0, 0, 94, 0, 2, 98, 3, 5, 350, 0, 1000, 5], np.zeros(13, np.int64)]),
+            g.integers(0, 70, size=30), np.full(30, 96), np.full(30, 25), np.full(30, 1)]
+    rows = [7, 5_000, 300, 9, 2_000]
+    B, T = 30, len(rows)
+    c = W.Config(171, "rebase", E, dtype, -1.0, 1.0, B, [W.TableSpec(m, "fixed", 1, 1, 1, "uniform") for m in rows])
+    c.value_seeds = [W.value_seed(171, t) for t in range(T)]
+    off = np.zeros(T * B + 1, np.int64)
+    np.cumsum(np.concatenate(lens), out=off[1:])
+    idx = np.concatenate([g.integers(0, m, size=int(x.sum())) for m, x in zip(rows, lens)])
+    idx[g.random(idx.size) < 0.02] = -1
+    # one worker and a stated pooling of 1: chunks of several bags, far more lookups than stated
+    stats = [{"mean_pooling": 1.0, "max_pooling": 0}] * T
+    hw = host_tables(c, W.VAL_INTEGER)
+    plan = far.Plan(rows, E, dtype, stats, B, num_workers=1, pooling=pooling).bind(upload_tables(hw))
+    info = plan.info()
+    assert info["kernel"] == "gather_kernel" and info["gather_steps"] == 12
+    d_idx, d_off = to_device(W.Batch(B, T, idx, off))
+    for w in (None, g.integers(-3, 4, size=idx.size).astype(np.float32)):
+        out = torch.full((B, T, E), float("nan"), device="cuda")
+        plan.lookup(d_idx, d_off, B, out, weights=None if w is None else torch.from_numpy(w).cuda())
+        torch.cuda.synchronize()
+        ref, mag, bad = OP.pool_reference(hw, idx, off, B, psw=w, pooling=pooling)
+        if pooling == "sum":
+            assert np.array_equal(out.cpu().numpy(), ref)
+        else:   # a division by the length as a multiplication: two roundings of half an ulp
+            assert OP.pooled_error(out.cpu().numpy(), ref, mag) <= 2.0 ** -22
+        assert plan.check_errors() == bad
