@@ -291,6 +291,19 @@ const char* emb_status_string(emb_status_t s);
 emb_status_t emb_debug_check_input(const emb_plan_t* plan, const int64_t* indices, const int64_t* offsets,
                                    const float* weights, int32_t batch, void* stream);
 
+/* ---- run queues (tests of the kernel choice and of the work's division) -----------------
+ * Text of the gather slices as the kernels walk them: a line "kernel <name> lanes <n> walker
+ * <wavefront | slots | sw> steps <n>" (walker: gather_kernel's wavefronts; lookup_kernel's
+ * matrix slots or sub-wavefronts), then one line per run of a worker's queues: worker, queue
+ * (wave, single or multi), table, batch slice, slices, bags per chunk.  Written as
+ * emb_plan_serialize writes.  emb_debug_queue_text is host only: the plan that emb_plan_text
+ * makes, on a device with 160 KiB of LDS per workgroup. */
+emb_status_t emb_debug_queue_text(int32_t num_tables, const int64_t* rows, int32_t embedding_dim,
+                                  emb_dtype_t dtype, const emb_table_stats_t* stats, int32_t max_batch,
+                                  int32_t num_workers, const emb_plan_options_t* opts, char* buf,
+                                  size_t cap, size_t* len_out);
+emb_status_t emb_debug_plan_queues(const emb_plan_t* plan, char* buf, size_t cap, size_t* len_out);
+
 /* ---- index-handling probes (tests of the exact integer work) ---------------------------
  * Both run the same device functions as emb_lookup on one workgroup. */
 

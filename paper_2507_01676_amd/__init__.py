@@ -42,7 +42,7 @@ MAX_HOT_STATS = 4096
 EXPORTED = ["emb_plan_create", "emb_plan_create_noalloc", "emb_plan_bind_weights", "emb_lookup", "emb_lookup_weighted", "emb_plan_check_errors",
             "emb_plan_serialize", "emb_plan_get_info", "emb_plan_destroy", "emb_plan_text",
             "emb_status_string", "emb_debug_dedup_tile", "emb_debug_hot_probe", "embx_fill_table",
-            "emb_plan_set_trace", "emb_default_beta", "emb_debug_check_input"]
+            "emb_plan_set_trace", "emb_default_beta", "emb_debug_check_input", "emb_debug_queue_text", "emb_debug_plan_queues"]
 
 
 class EmbxError(RuntimeError):
@@ -91,6 +91,8 @@ _lib.emb_plan_get_info.argtypes = [_vp, ctypes.POINTER(_Info)]
 _lib.emb_plan_destroy.argtypes = [_vp]
 _lib.emb_plan_text.argtypes = [_i32, ctypes.POINTER(_i64), _i32, _i32, ctypes.POINTER(_Stats), _i32, _i32,
                                ctypes.POINTER(_Opts), ctypes.c_char_p, _sz, ctypes.POINTER(_sz)]
+_lib.emb_debug_queue_text.argtypes = _lib.emb_plan_text.argtypes
+_lib.emb_debug_plan_queues.argtypes = [_vp, ctypes.c_char_p, _sz, ctypes.POINTER(_sz)]
 _lib.emb_plan_set_trace.argtypes = [_vp, _vp, _sz, ctypes.POINTER(_sz)]
 _lib.emb_default_beta.argtypes = [_i32, ctypes.POINTER(ctypes.c_double), _i32]
 _lib.emb_debug_dedup_tile.argtypes = [_vp, _i32, _vp, _vp, _vp, _vp]
@@ -227,19 +229,29 @@ def default_beta(row_bytes: int) -> List[float]:
     return [float(x) for x in out]
 
 
-def plan_text(rows: Sequence[int], E: int, dtype, stats, max_batch: int, num_workers: int, **opts) -> str:
-    """The planner alone (host only): the canonical text of the plan for ``num_workers`` workers."""
+def _host_text(name: str, rows, E: int, dtype, stats, max_batch: int, num_workers: int, opts: dict) -> str:
     T = len(rows)
     m = _Marshal(rows, stats, opts, T)
+    fn = getattr(_lib, name)
     n = _sz(0)
-    code = _lib.emb_plan_text(T, m.rows, int(E), _dtype_code(dtype), m.stats, int(max_batch), int(num_workers),
-                              ctypes.byref(m.opts), None, 0, ctypes.byref(n))
+    code = fn(T, m.rows, int(E), _dtype_code(dtype), m.stats, int(max_batch), int(num_workers),
+              ctypes.byref(m.opts), None, 0, ctypes.byref(n))
     if code not in (OK, ERR_BUFFER_TOO_SMALL):
-        raise EmbxError(code, "emb_plan_text")
+        raise EmbxError(code, name)
     buf = ctypes.create_string_buffer(n.value + 1)
-    _check(_lib.emb_plan_text(T, m.rows, int(E), _dtype_code(dtype), m.stats, int(max_batch), int(num_workers),
-                              ctypes.byref(m.opts), buf, n.value + 1, ctypes.byref(n)), "emb_plan_text")
+    _check(fn(T, m.rows, int(E), _dtype_code(dtype), m.stats, int(max_batch), int(num_workers),
+              ctypes.byref(m.opts), buf, n.value + 1, ctypes.byref(n)), name)
     return buf.value.decode()
+
+
+def plan_text(rows: Sequence[int], E: int, dtype, stats, max_batch: int, num_workers: int, **opts) -> str:
+    """The planner alone (host only): the canonical text of the plan for ``num_workers`` workers."""
+    return _host_text("emb_plan_text", rows, E, dtype, stats, max_batch, num_workers, opts)
+
+
+def queue_text(rows: Sequence[int], E: int, dtype, stats, max_batch: int, num_workers: int, **opts) -> str:
+    """Kernel, walker and run queues of the same plan (host only)."""
+    return _host_text("emb_debug_queue_text", rows, E, dtype, stats, max_batch, num_workers, opts)
 
 
 class Plan:
@@ -344,6 +356,14 @@ class Plan:
         _lib.emb_plan_serialize(self._h, None, 0, ctypes.byref(n))
         buf = ctypes.create_string_buffer(n.value + 1)
         _check(_lib.emb_plan_serialize(self._h, buf, n.value + 1, ctypes.byref(n)), "emb_plan_serialize")
+        return buf.value.decode()
+
+    def queues(self) -> str:
+        """Kernel, walker and run queues of this plan (the text of ``queue_text``)."""
+        n = _sz(0)
+        _lib.emb_debug_plan_queues(self._h, None, 0, ctypes.byref(n))
+        buf = ctypes.create_string_buffer(n.value + 1)
+        _check(_lib.emb_debug_plan_queues(self._h, buf, n.value + 1, ctypes.byref(n)), "emb_debug_plan_queues")
         return buf.value.decode()
 
     def info(self) -> dict:

@@ -100,9 +100,10 @@ def build(verbose: bool = False) -> str:
     cmds.append([hipcc, *HIP_FLAGS, "-x", "hip", "-c", os.path.join(CSRC, "api.cpp"), "-o", o])
     objs.append(o)
     # the planner is plain host C++: every binary64 operation rounds as written
-    o = os.path.join(BUILD, "planner.o")
-    cmds.append(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "planner.cpp"), "-o", o])
-    objs.append(o)
+    for name in ("planner", "queues"):
+        o = os.path.join(BUILD, f"{name}.o")
+        cmds.append(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, f"{name}.cpp"), "-o", o])
+        objs.append(o)
     _run_all(cmds, verbose)
     for lib, parts in ((FAR_LIB, [far.get(o, o) for o in objs]), (LIB, objs)):
         tmp = lib + ".tmp"

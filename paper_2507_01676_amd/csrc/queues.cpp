@@ -1,0 +1,352 @@
+// Kernel choice and run queues of a plan's gather slices (queues.hpp).
+#include "queues.hpp"
+
+#include <algorithm>
+#include <climits>
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+namespace embx {
+
+int lanes_per_row(int32_t R) {
+  int g = 1;
+  while (g * 16 < R) g <<= 1;
+  return g;
+}
+
+bool gather_only(const PlanOut& P) {
+  for (const PSlice& x : P.slices)
+    if (x.strat != S_GATHER) return false;
+  return true;
+}
+
+// Gather-only plans take at least two lanes per row (of a 16-byte row the second idles).
+// Alone, a lane would hold all the ids, weights and bag ends that a SW's lanes share: such
+// kernels spilled 300-500 registers, and their scratch costs each launch several us.  One
+// lane against two: 8 tables of 4332 one-lookup fp16 bags 10.8 -> 5.0 us, 12 weighted tables
+// at batch 1 24.1 -> 13.4, 8M lookups in bags of 40 75.0 -> 72.3, 49.6 in fp32 (73.3); fp16
+// bags of 8, 1.6M lookups, 18.9 -> 20.5 (24.6 before matrix slots).  Staged plans keep one
+// lane: their LDS rows lose more by half the SWs (all-LDS fp32 8.3 -> 9.5 ms, HOT 62 -> 71 us).
+int plan_lanes(const PlanOut& P) {
+  return gather_only(P) ? std::max(2, lanes_per_row(P.R)) : lanes_per_row(P.R);
+}
+
+bool runs_gather_kernel(const PlanOut& P) {
+  const char* env_kernel = std::getenv("EMBX_GATHER_KERNEL");
+  const int G = lanes_per_row(P.R);
+  // (the kernel offsets a few samples' outputs in 32 bits)
+  return (G == 16 || G == 32 || G == 64) && gather_only(P) &&
+         static_cast<int64_t>(P.T) * P.E < (int64_t(1) << 28) &&
+         !(env_kernel && std::strcmp(env_kernel, "classic") == 0);
+}
+
+namespace {
+
+// a slice of the plan, as far as the queues go
+struct Item {
+  int32_t table, strat, j, k;
+  int32_t mode;   // gather: 1 = a wavefront per bag
+};
+
+}  // namespace
+
+int gather_queues(const QueueIn& in, GatherQueues* q) {
+  const PlanOut& P = *in.plan;
+  const emb_table_stats_t* stats = in.stats;
+  const int64_t* rows = in.rows;
+  const int32_t* mean = in.mean;
+  const int32_t max_batch = in.max_batch;
+  const bool wave_gather = in.wave_gather;
+  const bool f16 = P.f16;
+  const bool staged = !gather_only(P);
+  const int K = P.K, G = plan_lanes(P), block = kBlock;
+
+  // slices in worker order
+  std::vector<Item> items;
+  std::vector<int32_t> wg_ptr(K + 1, 0);
+  items.reserve(P.slices.size());
+  for (const PSlice& x : P.slices) {
+    items.push_back(Item{x.t, x.strat, x.j, x.k, 0});
+    wg_ptr[x.wg + 1] += 1;
+  }
+  for (int w = 0; w < K; ++w) wg_ptr[w + 1] += wg_ptr[w];
+  // Gather slices share their worker's SW pool, so for them a bag is long when it
+  // holds more lookups than one SW's share of the worker's gather lookups.
+  for (int w = 0; w < K; ++w) {
+    double Wg = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      const Item& d = items[i];
+      if (d.strat != S_GATHER) continue;
+      const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+      Wg += static_cast<double>(nb) * std::max(1.0, stats[d.table].mean_pooling);
+    }
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      Item& d = items[i];
+      if (d.strat != S_GATHER) continue;
+      const double s_t = stats[d.table].mean_pooling;
+      d.mode = (s_t >= 4.0 * (64 / G) && s_t * (kBlock / G) > Wg) ? 1 : 0;
+    }
+  }
+
+  // gather run queues per worker, slices in plan order: wave-mode runs, then runs of
+  // tables whose bags hold at most one lookup (kChunkSingle bags per chunk: one step
+  // of a SW), then SW-mode runs.  SW-mode chunks carry about sqrt(5 W / NSW) expected
+  // lookups (W: the worker's SW-mode lookups at the max batch), at least one full step
+  // (8) and at most 128; wave-mode chunks carry about four wavefront steps of lookups,
+  // fewer when that leaves some of the 16 wavefronts without one.
+  //
+  // The wave-uniform gather kernel's queues are single-lookup bags (chunks of one wavefront
+  // step: ksteps S bags) and all other bags, in chunks of about 128 expected lookups, 192 when
+  // the worker's queue gives each wavefront at least 64 chunks (W / 16 >= 64 * 192, W the
+  // worker's lookups in that queue), and at least two wavefront steps (EMBX_WAVE_CHUNK
+  // overrides it).  Measured on workloads 3-5: shorter chunks keep a worker's wavefronts
+  // on fewer tables at a time, so their rows share L2; much shorter ones pay the per-chunk
+  // start (workload 5: 4358 us at 64 lookups, 4042 at 192, 4170 at 512).
+  const char* env_chunk = std::getenv("EMBX_WAVE_CHUNK");
+  const double wave_chunk_override = env_chunk ? std::atof(env_chunk) : 0.0;
+  // Rows in flight per step of the wave-uniform gather kernel (one build per choice): the
+  // choice with the fewest row rounds -- a chunk of c expected lookups takes ceil(c / N)
+  // steps of N = ks S lookups -- over the plan's multi-lookup chunks, ties to the larger
+  // (more rows in flight for the same rounds); plans without such chunks keep 12 (their
+  // single-lookup chunks are one step each, and larger steps make fewer of them).  Measured
+  // (12 / 13 / 16): workload 4's 100-lookup chunks (two bags of 50) take 3 / 2 / 2 steps and
+  // ran 14.36 / 14.03 / 13.92 us and, in a second session, 14.08 / 13.86 / 13.75 us; workload 5
+  // (chunks of ~180 lookups, N = 2 ks) 3966 / 3949 / 3929 us; workload 3 119.3 / 119.9 /
+  // 119.1 us; workload 2, single-lookup bags only, 5.30 / 5.36 / 5.51 us.
+  // EMBX_GATHER_STEPS = 12, 13 or 16 overrides it.
+  int ksteps = 12;
+  // Bags per chunk of worker w's multi-lookup items for steps of N lookups (item_cb): as many
+  // lookups as each wavefront's share of what is left of the queue, so that a queue shorter
+  // than 16 full chunks still occupies all 16 wavefronts and a longer one ends in small
+  // chunks; not below half a step (or the share of the whole queue), where a chunk's start
+  // costs more than it evens out, nor above the cap described above; at most 64 bags, the bag
+  // ends a wavefront holds.  Measured against the cap alone: 60k lookups of 1-KB rows (15 per
+  // wavefront) 19.5 -> 12.6 us, 72k lookups of 384-byte rows 34.2 -> 33.6 us, 3.4M lookups of
+  // 256-byte rows 108.9 -> 107.5 us; half or twice the share: within 2% of it.
+  std::vector<int32_t> item_cb(items.size(), 1);
+  auto multi_lookup = [&](const Item& d) { return d.strat == S_GATHER && stats[d.table].max_pooling != 1; };
+  auto bag_lookups = [&](const Item& d) { return std::max(1.0, stats[d.table].mean_pooling); };
+  auto slice_lookups = [&](const Item& d) {
+    const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+    return static_cast<double>(nb) * bag_lookups(d);
+  };
+  auto wave_chunks = [&](int w, double N) {
+    const int nwaves = block / 64;
+    double W = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
+      if (multi_lookup(items[i])) W += slice_lookups(items[i]);
+    const double cap = std::max(2.0 * N, W / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
+    const double least = std::min(0.5 * N, W / nwaves);
+    double left = W;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      const Item& d = items[i];
+      if (!multi_lookup(d)) continue;
+      const double target = wave_chunk_override > 0.0 ? wave_chunk_override
+                                                      : std::min(cap, std::max(least, left / nwaves));
+      item_cb[i] = static_cast<int32_t>(std::min(64.0, std::max(1.0, std::floor(target / bag_lookups(d)))));
+      left -= slice_lookups(d);
+    }
+  };
+  // Narrow rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one by
+  // one.  In slots a chunk is bags of one slice, one or more per SW, so the slices must hold
+  // bags for half of a wavefront's S SWs (1.6M lookups in bags of 8, 30 per slice: 18.1 us
+  // against 25.0; bags of 30, 3 per slice of 800 queries: 19.9 against 15.6).  fp16 rows of 4
+  // and 8 lanes also pay conversions: they gain on bags of up to 12 where each SW of the worker
+  // has at least 16 lookups (0.5M lookups in bags of 4: 26.1 against 27.1 us, 4M 313 / 349, 8M in
+  // bags of 8 198 / 206, of 24 360 / 347; 160k in bags of 8, 5 per SW: 12.0 / 11.1) and on bags
+  // of up to 3 (2 at 500 queries: 6.5 / 9.4).
+  if (!wave_gather && !staged && (G == 2 || G == 4 || G == 8)) {
+    const double S = 64.0 / G;
+    double bags = 0.0, lookups = 0.0, filled = 0.0;
+    for (const Item& d : items)
+      if (multi_lookup(d)) {
+        const double n = slice_lookups(d), nb = n / bag_lookups(d);
+        bags += nb;
+        lookups += n;
+        filled += n * std::min(1.0, nb / S);
+      }
+    q->slots = bags > 0.0 && filled >= 0.5 * lookups;
+    if (f16 && G >= 4) {
+      const double per_sw = lookups / (static_cast<double>(K) * (block / G));
+      q->slots = q->slots && ((lookups <= 3.0 * bags && (per_sw <= 3.0 || per_sw >= 8.0)) ||
+                              (lookups <= 12.0 * bags && per_sw >= 16.0));
+    }
+  }
+  // The same for the rows that lookup_kernel walks in matrix slots, whose chunks are S = 64 / G SWs
+  // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue.
+  auto narrow_chunks = [&](int w) {
+    const int S = 64 / G, M = std::min(4, G), nwaves = block / 64;
+    double left = 0.0;
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
+      if (multi_lookup(items[i])) left += slice_lookups(items[i]);
+    for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+      const Item& d = items[i];
+      if (!multi_lookup(d)) continue;
+      const double m = std::floor(left / (nwaves * S * bag_lookups(d)));
+      item_cb[i] = S * static_cast<int32_t>(std::min(static_cast<double>(M), std::max(1.0, m)));
+      left -= slice_lookups(d);
+    }
+  };
+  if (wave_gather) {
+    const char* env_steps = std::getenv("EMBX_GATHER_STEPS");
+    if (env_steps && *env_steps) {
+      ksteps = std::atoi(env_steps);
+      bool known = false;
+      for (int c : kGatherStepChoices) known = known || c == ksteps;
+      if (!known) {
+        return EMB_ERR_INVALID_ARGUMENT;
+      }
+    } else {
+      double best = -1.0;
+      for (int cand : kGatherStepChoices) {
+        const double N = static_cast<double>(cand) * (64 / G);
+        double rounds = 0.0;
+        for (int w = 0; w < K; ++w) {
+          wave_chunks(w, N);
+          for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+            const Item& d = items[i];
+            if (!multi_lookup(d)) continue;
+            const double s_t = bag_lookups(d), cb = item_cb[i];
+            const double nc = std::ceil(static_cast<double>((static_cast<int64_t>(max_batch) + d.k - 1) / d.k) / cb);
+            rounds += nc * std::ceil(cb * s_t / N);
+          }
+        }
+        if (best < 0.0 || rounds <= best) {   // candidates ascend: ties go to the larger
+          best = rounds;
+          ksteps = cand;
+        }
+      }
+      if (best == 0.0) ksteps = 12;   // no multi-lookup chunks
+    }
+  }
+  std::vector<GatherRun> gr;                       // runs, worker-major
+  std::vector<int32_t> gr_ptr(K + 1, 0);
+  std::vector<GatherSlotHeader> gr_head(K);
+  int max_runs = 0;
+  {
+    const int nsw = kBlock / G;
+    const int nwaves = block / 64;
+    const double wave_chunk = 4.0 * 8.0 * (64 / G);
+    auto slice_bags = [&](const Item& d) -> int64_t {
+      return (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+    };
+    // Slice j of k holds floor((j+1)B/k) - floor(jB/k) bags at the runtime batch B, which
+    // for some B < max_batch is one more than at max_batch (e.g. k = 256, j = 10: 3 bags at
+    // B = 1000, 4 at B = 792).  Every B <= max_batch gives at most ceil(max_batch / k), so a
+    // run gets chunks for that many; chunks past the slice at the runtime batch are empty
+    // and skipped by the kernel's queue.
+    auto slice_bags_any = [&](const Item& d) -> int64_t {
+      return (static_cast<int64_t>(max_batch) + d.k - 1) / d.k;
+    };
+    for (int w = 0; w < K; ++w) {
+      double Ws = 0.0, Ww = 0.0;
+      // classes, in queue order: 0 wave mode, 1 single-lookup bags, 2 SW mode.  Only a
+      // table whose statistics state a maximum of one lookup per bag is single-lookup; an
+      // unknown maximum (0) walks in SW mode
+      auto class_of = [&](const Item& d) -> int {
+        if (d.mode && !wave_gather) return 0;
+        return stats[d.table].max_pooling == 1 ? 1 : 2;
+      };
+      for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+        if (items[i].strat != S_GATHER) continue;
+        const double lk = static_cast<double>(slice_bags(items[i])) * std::max(1.0, stats[items[i].table].mean_pooling);
+        const int cls = class_of(items[i]);
+        if (cls == 0)
+          Ww += lk;
+        else if (cls == 2)
+          Ws += lk;
+      }
+      // SW-mode chunks are claimed dynamically: a chunk boundary costs about five lookups
+      // of a SW's time and the worker's tail is up to one chunk, so ~sqrt(5 W / NSW)
+      // lookups per chunk balances the two; measured, chunks past ~128 lookups lose again
+      // (the SWs then work on fewer tables at a time), hence the cap
+      const double target = std::min(128.0, std::max(8.0, std::floor(std::sqrt(5.0 * Ws / nsw))));
+      if (wave_gather) wave_chunks(w, static_cast<double>(ksteps) * (64 / G));
+      else if (q->slots) narrow_chunks(w);
+      const double wtarget = std::min(wave_chunk, std::max(1.0, std::floor(Ww / nwaves)));
+      gr_ptr[w] = static_cast<int32_t>(gr.size());
+      int64_t base[3] = {0, 0, 0};
+      int32_t nrun[3] = {0, 0, 0};
+      for (int cls = 0; cls < 3; ++cls) {
+        for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
+          const Item& d = items[i];
+          if (d.strat != S_GATHER || class_of(d) != cls) continue;
+          const double s_t = std::max(1.0, stats[d.table].mean_pooling);
+          const int32_t cb = cls == 1 ? (wave_gather ? ksteps * (64 / G) : kChunkSingle)
+                             : cls == 2 && (wave_gather || q->slots) ? item_cb[i]
+                                      : static_cast<int32_t>(std::max(1.0, std::floor((cls == 0 ? wtarget : target) / s_t)));
+          const int64_t nc = (slice_bags_any(d) + cb - 1) / cb;
+          if (nc == 0) continue;
+          GatherRun r{};
+          r.w = nullptr;
+          r.rows = rows[d.table];
+          r.table = d.table;
+          r.j = d.j;
+          r.k = d.k;
+          r.cb = cb;
+          r.chunk_base = static_cast<int32_t>(base[cls]);
+          r.mean = mean[d.table];
+          gr.push_back(r);
+          base[cls] += nc;
+          nrun[cls] += 1;
+        }
+      }
+      // the worker's header and runs are copied into LDS (all of a workgroup's LDS but
+      // the kernel's own static variables)
+      if (base[0] > INT32_MAX || base[1] > INT32_MAX || base[2] > INT32_MAX ||
+          nrun[0] + nrun[1] + nrun[2] > in.run_cap - 1) {
+        return EMB_ERR_UNSUPPORTED;
+      }
+      max_runs = std::max(max_runs, nrun[0] + nrun[1] + nrun[2]);
+      for (int cls = 0; cls < 3; ++cls) q->n_runs[cls] += nrun[cls];
+      GatherSlotHeader& hd = gr_head[w];
+      std::memset(&hd, 0, sizeof hd);
+      hd.n_wave = nrun[0];
+      hd.wave_chunks = static_cast<int32_t>(base[0]);
+      hd.n_single = nrun[1];
+      hd.single_chunks = static_cast<int32_t>(base[1]);
+      hd.sw_chunks = static_cast<int32_t>(base[2]);
+      hd.n_runs = nrun[0] + nrun[1] + nrun[2];
+    }
+    gr_ptr[K] = static_cast<int32_t>(gr.size());
+  }
+  // fixed-size slots, so that a worker fetches its header and runs in one round trip
+  q->slot = max_runs + 1;
+  q->records.assign(static_cast<size_t>(K) * q->slot, GatherRun{});
+  for (int w = 0; w < K; ++w) {
+    const size_t s0 = static_cast<size_t>(w) * q->slot;
+    std::memcpy(&q->records[s0], &gr_head[w], sizeof(GatherSlotHeader));
+    for (int32_t i = gr_ptr[w]; i < gr_ptr[w + 1]; ++i) {
+      q->records[s0 + 1 + (i - gr_ptr[w])] = gr[i];
+      q->run_at.emplace_back(s0 + 1 + (i - gr_ptr[w]), gr[i].table);
+    }
+  }
+  q->ksteps = wave_gather ? ksteps : 0;
+  return EMB_OK;
+}
+
+std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int ksteps, int slot,
+                        const std::vector<GatherRun>& records) {
+  static const char* const names[] = {"wave", "single", "multi"};
+  char line[160];
+  std::snprintf(line, sizeof line, "kernel %s lanes %d walker %s steps %d\n",
+                wave_gather ? "gather_kernel" : "lookup_kernel", plan_lanes(P),
+                wave_gather ? "wavefront" : slots ? "slots" : "sw", ksteps);
+  std::string s = line;
+  for (int w = 0; w < P.K; ++w) {
+    const GatherRun* const r = &records[static_cast<size_t>(w) * slot];
+    GatherSlotHeader hd;
+    std::memcpy(&hd, r, sizeof hd);
+    for (int i = 0; i < hd.n_runs; ++i) {
+      const int cls = i < hd.n_wave ? 0 : i < hd.n_wave + hd.n_single ? 1 : 2;
+      std::snprintf(line, sizeof line, "%d %s %d %d %d %d\n", w, names[cls], r[1 + i].table, r[1 + i].j, r[1 + i].k,
+                    r[1 + i].cb);
+      s += line;
+    }
+  }
+  return s;
+}
+
+}  // namespace embx

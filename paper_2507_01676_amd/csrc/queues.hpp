@@ -1,0 +1,50 @@
+// The gather slices of a plan as the kernels walk them: which kernel, how many lanes a row
+// takes, and every worker's queues of chunks.  Pure host code (no HIP calls).
+#pragma once
+
+#include <cstdint>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "../../include/embx.h"
+#include "device_types.hpp"
+#include "planner.hpp"
+
+namespace embx {
+
+int lanes_per_row(int32_t R);
+bool gather_only(const PlanOut& P);
+// lanes of a row in every kernel this plan launches
+int plan_lanes(const PlanOut& P);
+// the plan runs gather_kernel (else lookup_kernel)
+bool runs_gather_kernel(const PlanOut& P);
+
+struct QueueIn {
+  const PlanOut* plan;
+  const emb_table_stats_t* stats;   // per table
+  const int64_t* rows;
+  const int32_t* mean;              // per table: 1 = mean pooling
+  int32_t max_batch;
+  bool wave_gather;                 // runs_gather_kernel
+  int64_t run_cap;                  // records a worker's slot may take in LDS
+};
+
+struct GatherQueues {
+  bool slots = false;               // lookup_kernel sums multi-lookup bags in matrix slots
+  int ksteps = 0;                   // gather_kernel: row loads in flight per lane per step
+  int slot = 1;                     // records per worker: a GatherSlotHeader, then its runs
+  std::vector<GatherRun> records;   // [K * slot]; table pointers are set at bind
+  std::vector<std::pair<size_t, int32_t>> run_at;   // (record, table) of every run
+  int32_t n_runs[3] = {0, 0, 0};    // over all workers: wave mode, single-lookup bags, the rest
+};
+
+// 0 on success, otherwise an emb_status_t code.
+int gather_queues(const QueueIn& in, GatherQueues* out);
+
+// One line of kernel, lanes, walker and steps, then one per run: worker, queue, table, batch
+// slice, slices, bags per chunk.
+std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int ksteps, int slot,
+                        const std::vector<GatherRun>& records);
+
+}  // namespace embx

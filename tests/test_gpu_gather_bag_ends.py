@@ -2,7 +2,8 @@
 lookups of G-lane rows), around the groups of four instructions that a short step skips, and
 around a whole step; runs of empty bags; the most bags a chunk takes; rows and weights that
 are infinite or NaN, which belong to their own bag only; and a narrow table past 4 GiB.  Wide
-rows (gather_kernel) and narrow ones (lookup_kernel: in matrix slots, or by sub-wavefronts).
+rows (gather_kernel) and narrow ones (lookup_kernel, mostly by sub-wavefronts; in matrix slots:
+test_gpu_slots.py).
 Integer tables, bit-exact against the oracle."""
 import numpy as np
 import pytest
