@@ -114,7 +114,7 @@ EMBX_DECL_GATHER(16)
 #undef EMBX_DECL_GATHER
 
 // Host-callable launchers (defined in lookup.hip).  slots: the kernel whose multi-lookup gather
-// queue is cut for wavefronts that sum bags in matrix slots (gather-only plans, G 2 to 8).
+// queue is cut for wavefronts that sum bags in matrix slots (gather-only fp32 plans, G 2 to 8).
 int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, bool slots, int grid,
                   int lds_bytes, void* stream);
 int launch_gather(const LookupArgs& a, int G, bool f16, bool weighted, int ks, int grid, int block, int lds_bytes,

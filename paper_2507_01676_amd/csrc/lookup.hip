@@ -47,7 +47,7 @@
 
 // The lookup kernels are compiled in parts so that a build can run the parts in
 // parallel: EMBX_PART 0..3 holds the kernels of one (row type, weighted) pair, part 4
-// the probes, the table filler and the launch code, parts 5..8 the pair's kernels of
+// the probes, the table filler and the launch code, parts 5 and 6 the fp32 kernels of
 // gather-only plans with rows in matrix slots (their control is wave-uniform, see
 // build.py).  Without EMBX_PART one compile holds everything.
 #ifndef EMBX_PART
@@ -1536,10 +1536,11 @@ __device__ __forceinline__ int64_t slot_bcast64(int64_t v) {
   return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
 }
 
-template <int G, bool F16, bool W>
+template <int G, bool W>
 struct Slots {
+  static_assert(G == 2 || G == 4 || G == 8, "whole SWs per block of 4 lanes, or whole blocks per SW");
   static constexpr int S = kWave / G, M = G < 4 ? G : 4;
-  static constexpr int NA = F16 ? 8 : 4;
+  static constexpr int NA = 4;
   static constexpr int kUS = 8;               // rows in flight per SW (16 spill registers)
   static constexpr int IPL = kUS / G;         // ids per lane of a step: lane c holds lookups c, c + G, ...
 
@@ -1671,22 +1672,10 @@ struct Slots {
           const int one = W ? sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0])) : 0x3f800000;
           const float f = __int_as_float(__builtin_amdgcn_sbfe(static_cast<int>(in_slot), u, 1) & one);
           const i32x4 x = raw[u];
-          if constexpr (!F16) {
-            d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
-            d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
-            d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
-            d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
-          } else {
-            const int h[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const uint32_t v = static_cast<uint32_t>(h[i]);
-              d[2 * i] = __builtin_amdgcn_mfma_f32_4x4x1f32(
-                  f, __half2float(__ushort_as_half(static_cast<unsigned short>(v & 0xffffu))), d[2 * i], 0, 0, 0);
-              d[2 * i + 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(
-                  f, __half2float(__ushort_as_half(static_cast<unsigned short>(v >> 16))), d[2 * i + 1], 0, 0, 0);
-            }
-          }
+          d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
+          d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
+          d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
+          d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
         });
         if (!more) break;
       }
@@ -1703,12 +1692,11 @@ struct Slots {
         const int hi = G < 4 ? (lane & 3) / G * G : 0;   // first register of this lane's SW
         static_for<M>([&](auto r) __attribute__((always_inline)) {
           constexpr int rr = decltype(r)::value;
-          Acc<F16> acc;
+          Acc<false> acc;
 #pragma unroll
           for (int i = 0; i < NA; ++i) {
             float v = d[i][rr];
             if constexpr (G == 2) v = hi ? d[i][rr + 2] : v;
-            if constexpr (G == 1) v = hi == 0 ? d[i][0] : hi == 1 ? d[i][1] : hi == 2 ? d[i][2] : d[i][3];
             acc.v[i] = v;
           }
           if (mean) {
@@ -1725,7 +1713,7 @@ struct Slots {
           if (b >= cur.c1) break;
           GMEM const int64_t* off = as_global(a.offsets) + static_cast<int64_t>(table) * a.B + b;
           const int64_t k0 = off[0], k1 = off[1];
-          Acc<F16> acc;
+          Acc<false> acc;
           acc_zero(acc);
           for (int64_t k = k0; k < k1; ++k) {
             const int64_t x = as_global(a.indices)[k];
@@ -1798,10 +1786,11 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     static_cast<RowBase&>(f) = rb0;
     walk_single<G, F16, W>(idx, offsets, out, a.E, a.B, ost, l.lane_sw, f, q);
   }
-  if constexpr (SLOTS) {   // narrow rows: chunks taken by wavefronts
+  if constexpr (SLOTS) {   // narrow fp32 rows: chunks taken by wavefronts
+    static_assert(!F16, "");
     const int lane = l.tid & (kWave - 1);
-    Slots<G, F16, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
-                       lane, l.sw_w, lane & (Slots<G, F16, W>::M - 1)};
+    Slots<G, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
+                  lane, l.sw_w, lane & (Slots<G, W>::M - 1)};
     if (sw_chunks > 0) w.walk(l, rb0);
   } else {  // SW mode
     RunQueue q{runs, n_wave + n_single, nr, sw_chunks, a.B, true, qctr, l.lane_sw, G, l.sw, NSW};
@@ -1950,11 +1939,11 @@ __global__ void __launch_bounds__(256) fill_kernel(char* dst, int64_t row_begin,
 using KernelFn = void (*)(LookupArgs);
 
 // gather-only kernels whose multi-lookup queue is cut for Slots
-template <bool F16, bool W>
+template <bool W>
 KernelFn pick_slots(int G) {
-  if (G == 2) return &lookup_kernel<2, F16, false, W, true>;
-  if (G == 4) return &lookup_kernel<4, F16, false, W, true>;
-  if (G == 8) return &lookup_kernel<8, F16, false, W, true>;
+  if (G == 2) return &lookup_kernel<2, false, false, W, true>;
+  if (G == 4) return &lookup_kernel<4, false, false, W, true>;
+  if (G == 8) return &lookup_kernel<8, false, false, W, true>;
   return nullptr;
 }
 template <bool F16, bool STAGED, bool W>
@@ -1984,8 +1973,6 @@ LookupKernelFn lookup_kernel_f16(int G, bool staged);
 LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged);
 LookupKernelFn slots_kernel_f32(int G);
 LookupKernelFn slots_kernel_f32_weighted(int G);
-LookupKernelFn slots_kernel_f16(int G);
-LookupKernelFn slots_kernel_f16_weighted(int G);
 
 #if EMBX_HAS_PART(0)
 LookupKernelFn lookup_kernel_f32(int G, bool staged) {
@@ -2009,26 +1996,16 @@ LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged) {
 #endif
 
 #if EMBX_HAS_PART(5)
-LookupKernelFn slots_kernel_f32(int G) { return pick_slots<false, false>(G); }
+LookupKernelFn slots_kernel_f32(int G) { return pick_slots<false>(G); }
 #endif
 #if EMBX_HAS_PART(6)
-LookupKernelFn slots_kernel_f32_weighted(int G) { return pick_slots<false, true>(G); }
+LookupKernelFn slots_kernel_f32_weighted(int G) { return pick_slots<true>(G); }
 #endif
-#if EMBX_HAS_PART(7)
-LookupKernelFn slots_kernel_f16(int G) { return pick_slots<true, false>(G); }
-#endif
-#if EMBX_HAS_PART(8)
-LookupKernelFn slots_kernel_f16_weighted(int G) { return pick_slots<true, true>(G); }
-#endif
-
 #if EMBX_HAS_PART(4)
 namespace {
 
 LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted, bool slots) {
-  if (!staged && slots) {
-    if (f16) return weighted ? slots_kernel_f16_weighted(G) : slots_kernel_f16(G);
-    return weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
-  }
+  if (slots) return f16 || staged ? nullptr : weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
   if (f16) return weighted ? lookup_kernel_f16_weighted(G, staged) : lookup_kernel_f16(G, staged);
   return weighted ? lookup_kernel_f32_weighted(G, staged) : lookup_kernel_f32(G, staged);
 }

@@ -149,15 +149,16 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       left -= slice_lookups(d);
     }
   };
-  // Narrow rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one by
-  // one.  In slots a chunk is bags of one slice, one or more per SW, so the slices must hold
+  // Narrow fp32 rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one
+  // by one.  In slots a chunk is bags of one slice, one or more per SW, so the slices must hold
   // bags for half of a wavefront's S SWs (1.6M lookups in bags of 8, 30 per slice: 18.1 us
-  // against 25.0; bags of 30, 3 per slice of 800 queries: 19.9 against 15.6).  fp16 rows of 4
-  // and 8 lanes also pay conversions: they gain on bags of up to 12 where each SW of the worker
-  // has at least 16 lookups (0.5M lookups in bags of 4: 26.1 against 27.1 us, 4M 313 / 349, 8M in
-  // bags of 8 198 / 206, of 24 360 / 347; 160k in bags of 8, 5 per SW: 12.0 / 11.1) and on bags
-  // of up to 3 (2 at 500 queries: 6.5 / 9.4).
-  if (!wave_gather && !staged && (G == 2 || G == 4 || G == 8)) {
+  // against 25.0; bags of 30, 3 per slice of 800 queries: 19.9 against 15.6).  fp16 rows stay
+  // with the SWs: in slots they also pay conversions, which cost more than the slots save (rows
+  // of 64 and 128 bytes, 26 tables: bags of 2 at 1000 to 3000 queries 5.0-10.4 us by SWs, 6.4-15.0
+  // in slots; bags of 8 at 8192 queries 27.6 against 27.3 and 38.2 against 40.7, and 11.9-12.4
+  // against 14.8-15.2 where such a plan is called with 64 queries; rows of 32 bytes 23.9 / 23.3,
+  // with lognormal lengths 68 / 81, with 64 queries 10.3 / 13.4).
+  if (!wave_gather && !staged && !f16 && (G == 2 || G == 4 || G == 8)) {
     const double S = 64.0 / G;
     double bags = 0.0, lookups = 0.0, filled = 0.0;
     for (const Item& d : items)
@@ -168,11 +169,6 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
         filled += n * std::min(1.0, nb / S);
       }
     q->slots = bags > 0.0 && filled >= 0.5 * lookups;
-    if (f16 && G >= 4) {
-      const double per_sw = lookups / (static_cast<double>(K) * (block / G));
-      q->slots = q->slots && ((lookups <= 3.0 * bags && (per_sw <= 3.0 || per_sw >= 8.0)) ||
-                              (lookups <= 12.0 * bags && per_sw >= 16.0));
-    }
   }
   // The same for the rows that lookup_kernel walks in matrix slots, whose chunks are S = 64 / G SWs
   // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue.

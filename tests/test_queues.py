@@ -1,0 +1,34 @@
+"""Which walker and which queues a plan's gather slices get (emb_debug_queue_text, host only)."""
+import pytest
+
+import paper_2507_01676_amd as embx
+
+
+def queues(rows, E, dtype, stats, B, workers=256, **opts):
+    """(head of the text as a dict, runs as tuples)"""
+    lines = embx.queue_text(rows, E, dtype, stats, B, workers, **opts).splitlines()
+    f = lines[0].split()
+    return dict(zip(f[::2], f[1::2])), [tuple(x if i == 1 else int(x) for i, x in enumerate(ln.split())) for ln in lines[1:]]
+
+
+def tables(n, mean, most=0):
+    return [1000 + 40 * t for t in range(n)], [{"mean_pooling": mean, "max_pooling": most}] * n
+
+
+@pytest.mark.parametrize("batch", [64, 1000, 4096, 30000])
+@pytest.mark.parametrize("bag", [2.0, 3.0, 4.0, 8.0, 12.0, 30.0])
+@pytest.mark.parametrize("E", [8, 16, 24, 32, 64])
+def test_half_precision_rows_are_summed_by_sub_wavefronts(E, bag, batch):
+    rows, stats = tables(26, bag)
+    head, _ = queues(rows, E, "f16", stats, batch)
+    assert head["kernel"] == "lookup_kernel" and head["walker"] == "sw"
+
+
+@pytest.mark.parametrize("E,lanes", [(4, 2), (8, 2), (16, 4), (32, 8)])
+def test_single_precision_rows_take_slots_where_the_slices_hold_bags(E, lanes):
+    rows, stats = tables(26, 8.0)
+    head, _ = queues(rows, E, "f32", stats, 8192)   # 32 bags per slice: half of 32 SWs and more
+    assert head["lanes"] == str(lanes) and head["walker"] == "slots"
+    rows, stats = tables(26, 30.0)
+    head, _ = queues(rows, E, "f32", stats, 800)    # 3 bags per slice
+    assert head["walker"] == "sw"
