@@ -126,7 +126,10 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   // wavefront) 19.5 -> 12.6 us, 72k lookups of 384-byte rows 34.2 -> 33.6 us, 3.4M lookups of
   // 256-byte rows 108.9 -> 107.5 us; half or twice the share: within 2% of it.
   std::vector<int32_t> item_cb(items.size(), 1);
-  auto multi_lookup = [&](const Item& d) { return d.strat == S_GATHER && stats[d.table].max_pooling != 1; };
+  // (lookup_kernel's wave-mode slices have a queue of their own)
+  auto multi_lookup = [&](const Item& d) {
+    return d.strat == S_GATHER && stats[d.table].max_pooling != 1 && (wave_gather || !d.mode);
+  };
   auto bag_lookups = [&](const Item& d) { return std::max(1.0, stats[d.table].mean_pooling); };
   auto slice_lookups = [&](const Item& d) {
     const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;

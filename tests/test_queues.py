@@ -32,3 +32,21 @@ def test_single_precision_rows_take_slots_where_the_slices_hold_bags(E, lanes):
     rows, stats = tables(26, 30.0)
     head, _ = queues(rows, E, "f32", stats, 800)    # 3 bags per slice
     assert head["walker"] == "sw"
+
+
+def test_wave_mode_slices_do_not_decide_for_the_others():
+    # every bag is long: nothing is left for slots
+    rows, stats = tables(5, 40.0)
+    head, runs = queues(rows, 32, "f32", stats, 1100)
+    assert {r[1] for r in runs} == {"wave"} and head["walker"] == "sw"
+    # a table of long bags in slices of two holds most lookups; the others' slices hold enough bags
+    rows, stats = tables(26, 2.0)
+    stats = [{"mean_pooling": 100.0, "max_pooling": 0}] + stats[1:]
+    head, runs = queues(rows, 32, "f32", stats, 512)
+    assert {(r[1], r[2] == 0) for r in runs} == {("wave", True), ("multi", False)} and head["walker"] == "slots"
+    # ... and size their chunks by their own lookups alone: 342 bags of 4 on a worker, 2.7 bags per
+    # sub-wavefront of 16 wavefronts
+    rows, stats = tables(24, 4.0)
+    stats = [{"mean_pooling": 100.0, "max_pooling": 0}] * 4 + stats[4:]
+    _, runs = queues(rows, 32, "f32", stats, 1024)
+    assert {(r[4], r[5]) for r in runs if r[1] == "multi"} == {(3, 2 * 8)}
