@@ -60,6 +60,7 @@ struct GatherSlotHeader {
 static_assert(sizeof(GatherSlotHeader) == sizeof(GatherRun), "a slot header takes one run record");
 constexpr int kStaticLdsReserve = 1024;   // LDS kept for the kernel's static variables
 constexpr int kChunkSingle = 8;           // bags per chunk of a single-lookup-bag run (one SW step)
+constexpr int kSlotStep = 8;              // lookups of a SW per step in matrix slots
 
 struct LookupArgs {
   const DevItem* items;

@@ -1541,7 +1541,7 @@ struct Slots {
   static_assert(G == 2 || G == 4 || G == 8, "whole SWs per block of 4 lanes, or whole blocks per SW");
   static constexpr int S = kWave / G, M = G < 4 ? G : 4;
   static constexpr int NA = 4;
-  static constexpr int kUS = 8;               // rows in flight per SW (16 spill registers)
+  static constexpr int kUS = kSlotStep;       // rows in flight per SW (16 spill registers)
   static constexpr int IPL = kUS / G;         // ids per lane of a step: lane c holds lookups c, c + G, ...
 
   struct Chunk {   // bags [c0, c1) of run `run` (-1: none), and this lane's slot of it

@@ -174,7 +174,12 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     q->slots = bags > 0.0 && filled >= 0.5 * lookups;
   }
   // The same for the rows that lookup_kernel walks in matrix slots, whose chunks are S = 64 / G SWs
-  // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue.
+  // of 1 to min(4, G) bags each: the wavefront's share of what is left of the queue, and at least
+  // the bags that one step of kSlotStep lookups per SW holds, which cost no more than one bag (26
+  // tables at 2500 queries, 128-byte rows: bags of 1 9.4 -> 5.9 us, of 2 9.9 -> 6.2, 5.8 and 6.7 by
+  // SWs; 64-byte rows, 8 tables at 24000 queries: bags of 2 10.2 -> 7.3, 7.8 by SWs).  Bags of one
+  // lookup on 32-byte rows fill two of a step's eight rows: 624k of them 15.4 us, 13.8 by SWs (where
+  // lengths vary about a mean of 1, 0.6 of the SWs' time).
   auto narrow_chunks = [&](int w) {
     const int S = 64 / G, M = std::min(4, G), nwaves = block / 64;
     double left = 0.0;
@@ -183,8 +188,9 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
       const Item& d = items[i];
       if (!multi_lookup(d)) continue;
-      const double m = std::floor(left / (nwaves * S * bag_lookups(d)));
-      item_cb[i] = S * static_cast<int32_t>(std::min(static_cast<double>(M), std::max(1.0, m)));
+      const double share = std::floor(left / (nwaves * S * bag_lookups(d)));
+      const double step = std::max(1.0, std::floor(kSlotStep / bag_lookups(d)));
+      item_cb[i] = S * static_cast<int32_t>(std::min(static_cast<double>(M), std::max(step, share)));
       left -= slice_lookups(d);
     }
   };

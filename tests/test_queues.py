@@ -50,3 +50,16 @@ def test_wave_mode_slices_do_not_decide_for_the_others():
     stats = [{"mean_pooling": 100.0, "max_pooling": 0}] * 4 + stats[4:]
     _, runs = queues(rows, 32, "f32", stats, 1024)
     assert {(r[4], r[5]) for r in runs if r[1] == "multi"} == {(3, 2 * 8)}
+
+
+@pytest.mark.parametrize("E,sws,most", [(8, 32, 2), (16, 16, 4), (32, 8, 4)])
+@pytest.mark.parametrize("bag", [0.2, 1.0, 2.0, 3.0, 4.0, 5.0, 8.0, 9.0, 40.0])
+def test_a_slots_chunk_fills_a_step(E, sws, most, bag):
+    """However short the queue: a step holds 8 lookups per sub-wavefront."""
+    rows, stats = tables(26, bag)
+    for batch in (sws, 300, 2500, 20000):
+        head, runs = queues(rows, E, "f32", stats, batch, workers=32)
+        if head["walker"] == "slots":
+            bags = {r[5] for r in runs if r[1] == "multi"}
+            least = max(1, min(most, int(8 // max(1.0, bag))))
+            assert bags <= {sws * m for m in range(least, most + 1)}, (batch, bags)
