@@ -1509,7 +1509,12 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
 // for A and NA matrix instructions for S rows, and bag ends cost nothing inside a step: no
 // branch, no masked store, no copy of the sums.  Each step of D is an fma in lookup order
 // (bit for bit the sum the other walkers make).  A zero times an infinity or NaN would put a
-// NaN into the SW's other bags, so a chunk with any non-finite sum is summed again bag by bag.
+// NaN into the SW's other bags, so a chunk with any sum that is not finite is summed again by
+// selects (8 vector instructions per lookup and occupied slot), and so are the
+// chunks after it up to the first finite one.  1.7M lookups in bags of 8, 26 tables whose most
+// frequent row holds a NaN (half of the bags): 24.9, 25.3 and 40.3 us on 32-, 64- and 128-byte
+// rows (finite: 18.6, 20.2, 26.2; by SWs 21.9, 26.1, 35.8; again bag by bag, without loads in
+// flight: 36.6, 48.0, 86.0); a NaN in a rare row 20.1, 22.1, 29.2.
 // G < 4: a block holds 4 / G SWs, and a lane uses the part of D whose slots are its own SW's.
 //
 // What bounds it: the 128-byte lines beyond L2 (57 G/s on this device at any row size) on
@@ -1604,132 +1609,203 @@ struct Slots {
     }
   }
 
+  // A chunk's table, wave-uniform.
+  struct Table {
+    i32x4 rsrc;
+    uint32_t rows;
+    int table;
+    bool mean, big;   // big: past the descriptor's 32-bit offsets
+    GMEM const char* w;
+  };
+  __device__ __forceinline__ Table table_of(const Chunk& c) const {
+    const LMEM GatherRun& g = runs[uni(c.run)];
+    const uint64_t wb = reinterpret_cast<uint64_t>(g.w);
+    Table t;
+    t.rows = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(g.rows)));
+    t.rsrc.x = __builtin_amdgcn_readfirstlane(static_cast<int>(wb & 0xffffffffu));
+    t.rsrc.y = __builtin_amdgcn_readfirstlane(static_cast<int>(((wb >> 32) & 0xffffu) | (static_cast<uint32_t>(a.R) << 16)));
+    t.rsrc.z = static_cast<int>(t.rows);
+    t.rsrc.w = 0x00020000;
+    t.table = __builtin_amdgcn_readfirstlane(g.table);
+    t.mean = __builtin_amdgcn_readfirstlane(g.mean) != 0;
+    t.big = static_cast<uint64_t>(t.rows) * static_cast<uint64_t>(a.R) >= (uint64_t(1) << 32);
+    t.w = as_global(static_cast<const char*>(g.w));
+    return t;
+  }
+
+  // The rows (and weights) of a step's lookups, the ids loaded for position p on.
+  __device__ __forceinline__ void load_rows(const Table& t, const RowBase& rb0, int lane_sw, int64_t p, int64_t pend,
+                                            bool count, const int64_t (&id)[IPL], const float (&wt)[IPL],
+                                            i32x4 (&raw)[kUS], float (&wl)[IPL]) const {
+    int row[IPL];
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+      const bool in = p + lane_sw + j * G < pend;
+      const bool ok = static_cast<uint64_t>(id[j]) < t.rows;
+      if (count && in && !ok) atomicAdd(as_global(a.err), 1ull);
+      row[j] = ok ? static_cast<int>(id[j]) : t.big ? -1 : static_cast<int>(t.rows);
+      wl[j] = W && ok ? wt[j] : 0.0f;
+    }
+    if (!t.big) {
+      static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+        raw[u] = narrow_buffer_load(t.rsrc, sw_bcast<G, u % G>(row[u / G]), rb0.lane_c, 0, 0);
+      });
+    } else {
+      static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+        const int r = sw_bcast<G, u % G>(row[u / G]);
+        raw[u] = *reinterpret_cast<GMEM const i32x4*>((r >= 0 ? t.w + static_cast<int64_t>(r) * a.R : rb0.zero) +
+                                                      rb0.lane_c);
+      });
+    }
+  }
+
+  // this lane's slot in the step at p: a bit per lookup
+  __device__ __forceinline__ uint32_t slot_bits(const Chunk& c, int64_t p) const {
+    const int rs = static_cast<int>(max(int64_t(0), min64(c.st - p, kUS)));
+    const int re = static_cast<int>(max(int64_t(0), min64(c.en - p, kUS)));
+    return ((1u << re) - 1u) & ~((1u << rs) - 1u);
+  }
+
+  static __device__ __forceinline__ bool finite(const f32x4 (&d)[NA]) {
+    float t = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t = __builtin_fmaf(d[i][r], 0.0f, t);
+    return __ballot(!(t == 0.0f)) == 0;
+  }
+
+  // Stores the chunk's bags.  Register r of d holds slot r, where a block holds two SWs (G = 2)
+  // the registers from hi on this lane's.
+  __device__ __forceinline__ void store(const Chunk& c, const Table& t, const Lane& l, int hi, const f32x4 (&d)[NA]) const {
+    GMEM float* const ob = as_global(a.out) + static_cast<int64_t>(t.table) * a.E + l.lane_sw * NA;
+    const int64_t ost = static_cast<int64_t>(a.T) * a.E;
+    float scale = 1.0f;
+    if (t.mean && c.en - c.st > 1) scale = 1.0f / static_cast<float>(c.en - c.st);
+    static_for<M>([&](auto r) __attribute__((always_inline)) {
+      constexpr int rr = decltype(r)::value;
+      Acc<false> acc;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        float v = d[i][rr];
+        if constexpr (G == 2) v = hi ? d[i][rr + 2] : v;
+        acc.v[i] = v;
+      }
+      if (t.mean) {
+        const float sc = __int_as_float(slot_bcast<G, rr>(__float_as_int(scale)));
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc.v[i] *= sc;
+      }
+      const int b = c.c0 + sw * c.mp + rr;
+      if (rr < c.mp && b < c.c1 && l.active) acc_store(ob + static_cast<int64_t>(b) * ost, acc);
+    });
+  }
+
+  // Chunk c, its stream p, pend, id, wt begun (afterwards chunk nxt's), by selects: each row is
+  // added to its own bag and to no other, not even as a zero.  True if every sum is finite.
+  __device__ __forceinline__ bool sum_exact(const Chunk& c, const Chunk& nxt, const Lane& l, const RowBase& rb0, bool count,
+                                            int64_t& p, int64_t& pend, int64_t (&id)[IPL], float (&wt)[IPL]) const {
+    const Table t = table_of(c);
+    f32x4 d[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    while (true) {
+      i32x4 raw[kUS];
+      float wl[IPL];
+      load_rows(t, rb0, l.lane_sw, p, pend, count, id, wt, raw, wl);
+      const uint32_t in_slot = slot_bits(c, p);
+      p += kUS;
+      const bool more = __ballot(p < pend) != 0;
+      if (!more && nxt.run >= 0) {   // the first ids of the next chunk
+        p = slot_bcast64<G, 0>(nxt.st);
+        pend = slot_bcast64<G, M - 1>(nxt.en);
+      }
+      load_ids(p, pend, l.lane_sw, id, wt);
+      asm volatile("" ::: "memory");   // every load of the step is issued before its first use
+      static_for<M>([&](auto r) __attribute__((always_inline)) {
+        constexpr int rr = decltype(r)::value;
+        const uint32_t in = static_cast<uint32_t>(slot_bcast<G, rr>(static_cast<int>(in_slot)));
+        if (__ballot(in != 0) == 0) return;   // no SW is in this slot
+        static_for<kUS>([&](auto u) __attribute__((always_inline)) {
+          const float w = W ? __int_as_float(sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0]))) : rb0.one;
+          const float x[NA] = {__int_as_float(raw[u].x), __int_as_float(raw[u].y), __int_as_float(raw[u].z),
+                               __int_as_float(raw[u].w)};
+          const bool on = ((in >> u) & 1u) != 0;
+#pragma unroll
+          for (int i = 0; i < NA; ++i) d[i][rr] = on ? __builtin_fmaf(x[i], w, d[i][rr]) : d[i][rr];
+        });
+      });
+      if (!more) break;
+    }
+    store(c, t, l, 0, d);
+    return finite(d);
+  }
+
   __device__ __forceinline__ void walk(const Lane& l, const RowBase& rb0) {
     Chunk cur, nxt;
     claim(cur);
     if (uni(cur.run) < 0) return;
     claim(nxt);
-    int64_t p = slot_bcast64<G, 0>(cur.st), pend = slot_bcast64<G, M - 1>(cur.en);
-    int64_t id[IPL];
-    float wt[IPL];
-    load_ids(p, pend, l.lane_sw, id, wt);
-    const int64_t ost = static_cast<int64_t>(a.T) * a.E;
+    const int hi = G < 4 ? (lane & 3) / G * G : 0;   // first register of this lane's SW
     while (true) {
-      const LMEM GatherRun& g = runs[uni(cur.run)];
-      const uint64_t wb = reinterpret_cast<uint64_t>(g.w);
-      const uint32_t rows = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(g.rows)));
-      i32x4 rsrc;
-      rsrc.x = __builtin_amdgcn_readfirstlane(static_cast<int>(wb & 0xffffffffu));
-      rsrc.y = __builtin_amdgcn_readfirstlane(static_cast<int>(((wb >> 32) & 0xffffu) | (static_cast<uint32_t>(a.R) << 16)));
-      rsrc.z = static_cast<int>(rows);
-      rsrc.w = 0x00020000;
-      const int table = __builtin_amdgcn_readfirstlane(g.table);
-      const bool mean = __builtin_amdgcn_readfirstlane(g.mean) != 0;
-      // (the descriptor's offsets are 32 bits wide)
-      const bool big = static_cast<uint64_t>(rows) * static_cast<uint64_t>(a.R) >= (uint64_t(1) << 32);
-      f32x4 d[NA];
-#pragma unroll
-      for (int i = 0; i < NA; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      int64_t np = 0, npend = 0;
+      int64_t p = slot_bcast64<G, 0>(cur.st), pend = slot_bcast64<G, M - 1>(cur.en);
+      int64_t id[IPL];
+      float wt[IPL];
+      load_ids(p, pend, l.lane_sw, id, wt);
       while (true) {
-        int row[IPL];
-        float wl[IPL];
+        const Table t = table_of(cur);
+        f32x4 d[NA];
 #pragma unroll
-        for (int j = 0; j < IPL; ++j) {
-          const bool in = p + l.lane_sw + j * G < pend;
-          const bool ok = static_cast<uint64_t>(id[j]) < rows;
-          if (in && !ok) atomicAdd(as_global(a.err), 1ull);
-          row[j] = ok ? static_cast<int>(id[j]) : big ? -1 : static_cast<int>(rows);
-          wl[j] = W && ok ? wt[j] : 0.0f;
-        }
-        i32x4 raw[kUS];
-        if (!big) {
+        for (int i = 0; i < NA; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        int64_t np = 0, npend = 0;
+        while (true) {
+          i32x4 raw[kUS];
+          float wl[IPL];
+          load_rows(t, rb0, l.lane_sw, p, pend, true, id, wt, raw, wl);
+          const uint32_t in_slot = slot_bits(cur, p);
+          p += kUS;
+          const bool more = __ballot(p < pend) != 0;
+          if (more) {
+            load_ids(p, pend, l.lane_sw, id, wt);
+          } else if (nxt.run >= 0) {   // the first ids of the next chunk
+            np = slot_bcast64<G, 0>(nxt.st);
+            npend = slot_bcast64<G, M - 1>(nxt.en);
+            load_ids(np, npend, l.lane_sw, id, wt);
+          }
+          asm volatile("" ::: "memory");   // every load of the step is issued before its first use
           static_for<kUS>([&](auto u) __attribute__((always_inline)) {
-            raw[u] = narrow_buffer_load(rsrc, sw_bcast<G, u % G>(row[u / G]), rb0.lane_c, 0, 0);
+            const int one = W ? sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0])) : 0x3f800000;
+            const float f = __int_as_float(__builtin_amdgcn_sbfe(static_cast<int>(in_slot), u, 1) & one);
+            const i32x4 x = raw[u];
+            d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
+            d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
+            d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
+            d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
           });
-        } else {
-          static_for<kUS>([&](auto u) __attribute__((always_inline)) {
-            const int r = sw_bcast<G, u % G>(row[u / G]);
-            raw[u] = *reinterpret_cast<GMEM const i32x4*>(
-                (r >= 0 ? as_global(static_cast<const char*>(g.w)) + static_cast<int64_t>(r) * a.R : rb0.zero) + rb0.lane_c);
-          });
+          if (!more) break;
         }
-        // this lane's slot in the step: lookups [rs, re)
-        const int rs = static_cast<int>(max(int64_t(0), min64(cur.st - p, kUS)));
-        const int re = static_cast<int>(max(int64_t(0), min64(cur.en - p, kUS)));
-        const uint32_t in_slot = ((1u << re) - 1u) & ~((1u << rs) - 1u);
-        p += kUS;
-        const bool more = __ballot(p < pend) != 0;
-        if (more) {
-          load_ids(p, pend, l.lane_sw, id, wt);
-        } else if (nxt.run >= 0) {   // the first ids of the next chunk
-          np = slot_bcast64<G, 0>(nxt.st);
-          npend = slot_bcast64<G, M - 1>(nxt.en);
-          load_ids(np, npend, l.lane_sw, id, wt);
-        }
-        asm volatile("" ::: "memory");   // every load of the step is issued before its first use
-        static_for<kUS>([&](auto u) __attribute__((always_inline)) {
-          const int one = W ? sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0])) : 0x3f800000;
-          const float f = __int_as_float(__builtin_amdgcn_sbfe(static_cast<int>(in_slot), u, 1) & one);
-          const i32x4 x = raw[u];
-          d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
-          d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
-          d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
-          d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
-        });
-        if (!more) break;
+        if (!finite(d)) break;
+        store(cur, t, l, hi, d);
+        if (uni(nxt.run) < 0) return;
+        cur = nxt;
+        p = np;
+        pend = npend;
+        claim(nxt);
       }
-      // ---- store the chunk's bags: register r of d holds slot r (G < 4: of the block)
-      float t = 0.0f;
-#pragma unroll
-      for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t = __builtin_fmaf(d[i][r], 0.0f, t);
-      GMEM float* const ob = as_global(a.out) + static_cast<int64_t>(table) * a.E + l.lane_sw * NA;
-      if (__ballot(!(t == 0.0f)) == 0) {
-        float scale = 1.0f;
-        if (mean && cur.en - cur.st > 1) scale = 1.0f / static_cast<float>(cur.en - cur.st);
-        const int hi = G < 4 ? (lane & 3) / G * G : 0;   // first register of this lane's SW
-        static_for<M>([&](auto r) __attribute__((always_inline)) {
-          constexpr int rr = decltype(r)::value;
-          Acc<false> acc;
-#pragma unroll
-          for (int i = 0; i < NA; ++i) {
-            float v = d[i][rr];
-            if constexpr (G == 2) v = hi ? d[i][rr + 2] : v;
-            acc.v[i] = v;
-          }
-          if (mean) {
-            const float sc = __int_as_float(slot_bcast<G, rr>(__float_as_int(scale)));
-#pragma unroll
-            for (int i = 0; i < NA; ++i) acc.v[i] *= sc;
-          }
-          const int b = cur.c0 + sw * cur.mp + rr;
-          if (rr < cur.mp && b < cur.c1 && l.active) acc_store(ob + static_cast<int64_t>(b) * ost, acc);
-        });
-      } else {
-        for (int r = 0; r < cur.mp; ++r) {   // bag by bag (invalid ids have been counted)
-          const int b = cur.c0 + sw * cur.mp + r;
-          if (b >= cur.c1) break;
-          GMEM const int64_t* off = as_global(a.offsets) + static_cast<int64_t>(table) * a.B + b;
-          const int64_t k0 = off[0], k1 = off[1];
-          Acc<false> acc;
-          acc_zero(acc);
-          for (int64_t k = k0; k < k1; ++k) {
-            const int64_t x = as_global(a.indices)[k];
-            if (static_cast<uint64_t>(x) >= rows) continue;
-            acc_add(acc, ldg16(as_global(static_cast<const char*>(g.w)) + x * a.R + rb0.lane_c),
-                    W ? as_global(a.weights)[k] : rb0.one);
-          }
-          if (mean) acc_mean(acc, k1 - k0);
-          if (l.active) acc_store(ob + static_cast<int64_t>(b) * ost, acc);
-        }
+      // chunk cur again by selects (its invalid ids are counted), and the chunks after it up to
+      // the first whose sums are finite: rows that are not tend to be looked up often
+      bool count = false;
+      p = slot_bcast64<G, 0>(cur.st);
+      pend = slot_bcast64<G, M - 1>(cur.en);
+      load_ids(p, pend, l.lane_sw, id, wt);
+      while (true) {
+        const bool ok = sum_exact(cur, nxt, l, rb0, count, p, pend, id, wt);
+        if (uni(nxt.run) < 0) return;
+        cur = nxt;
+        claim(nxt);
+        if (ok) break;
+        count = true;
       }
-      if (uni(nxt.run) < 0) break;
-      cur = nxt;
-      p = np;
-      pend = npend;
-      claim(nxt);
     }
   }
 };
