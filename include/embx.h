@@ -293,8 +293,8 @@ emb_status_t emb_debug_check_input(const emb_plan_t* plan, const int64_t* indice
 
 /* ---- run queues (tests of the kernel choice and of the work's division) -----------------
  * Text of the gather slices as the kernels walk them: a line "kernel <name> lanes <n> walker
- * <wavefront | slots | sw> steps <n>" (walker: gather_kernel's wavefronts; lookup_kernel's
- * matrix slots or sub-wavefronts), then one line per run of a worker's queues: worker, queue
+ * <wavefront | slots | sw> steps <n> wave_lanes <n>" (walker: gather_kernel's wavefronts;
+ * lookup_kernel's matrix slots or sub-wavefronts; wave_lanes: a row's lanes in the wave queue), then one line per run of a worker's queues: worker, queue
  * (wave, single or multi), table, batch slice, slices, bags per chunk.  Written as
  * emb_plan_serialize writes.  emb_debug_queue_text is host only: the plan that emb_plan_text
  * makes, on a device with 160 KiB of LDS per workgroup. */

@@ -51,6 +51,7 @@ struct emb_plan {
   const char* d_zero_row = nullptr;      // R zero bytes
   bool staged = false;                   // the plan has LDS / HOT / DEDUP / STREAM slices
   bool slots = false;                    // lookup_kernel sums multi-lookup gather bags in matrix slots
+  int wave_lanes = 0;                    // lanes of a row in lookup_kernel's wave mode
   bool wave_gather = false;              // launches the wave-uniform gather kernel (gather.hip)
   int block = kBlock;                    // threads per worker
   int ksteps = 0;                        // gather_kernel: row loads in flight per lane per step
@@ -247,7 +248,7 @@ emb_status_t emb_debug_queue_text(int32_t num_tables, const int64_t* rows, int32
   GatherQueues q;
   const int qrc = gather_queues(QueueIn{&out, stats, rows, mean.data(), max_batch, wave_gather, kRunCap160K}, &q);
   if (qrc != 0) return st(qrc);
-  return write_text(queues_text(out, wave_gather, q.slots, q.ksteps, q.slot, q.records), buf, cap, len_out);
+  return write_text(queues_text(out, wave_gather, q.slots, q.wave_lanes, q.ksteps, q.slot, q.records), buf, cap, len_out);
 }
 
 static_assert(static_cast<int>(B_COUNT) == static_cast<int>(EMB_BETA_COUNT),
@@ -468,6 +469,7 @@ emb_status_t plan_create(emb_plan_t** plan_out, int32_t num_tables, const int64_
   p->h_gr_runs = std::move(q.run_at);
   p->gr_slot = q.slot;
   p->slots = q.slots;
+  p->wave_lanes = q.wave_lanes;
   for (int cls = 0; cls < 3; ++cls) p->gather_runs[cls] = q.n_runs[cls];
 
   // one metadata allocation
@@ -699,8 +701,9 @@ emb_status_t lookup_impl(emb_plan_t* plan, const int64_t* indices, const int64_t
   if (plan->wave_gather)
     return st(launch_gather(a, plan->G, plan->f16, weighted, plan->ksteps, plan->K, plan->block, plan->lds_bytes,
                             stream));
-  return st(launch_lookup(a, plan->G, plan->f16, plan->staged, weighted, plan->slots, plan->K, plan->lds_bytes,
-                          stream));
+  // (G = 1 of a gather-only plan: the kernels whose wave mode takes one lane per row)
+  return st(launch_lookup(a, plan->wave_lanes == 1 ? 1 : plan->G, plan->f16, plan->staged, weighted, plan->slots,
+                          plan->K, plan->lds_bytes, stream));
 }
 
 }  // namespace
@@ -745,7 +748,8 @@ emb_status_t emb_plan_serialize(const emb_plan_t* plan, char* buf, size_t cap, s
 
 emb_status_t emb_debug_plan_queues(const emb_plan_t* plan, char* buf, size_t cap, size_t* len_out) {
   if (!plan) return EMB_ERR_INVALID_ARGUMENT;
-  return write_text(queues_text(plan->plan, plan->wave_gather, plan->slots, plan->ksteps, plan->gr_slot, plan->h_gr),
+  return write_text(queues_text(plan->plan, plan->wave_gather, plan->slots, plan->wave_lanes, plan->ksteps,
+                                plan->gr_slot, plan->h_gr),
                     buf, cap, len_out);
 }
 

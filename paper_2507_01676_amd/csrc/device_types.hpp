@@ -116,6 +116,7 @@ EMBX_DECL_GATHER(16)
 
 // Host-callable launchers (defined in lookup.hip).  slots: the kernel whose multi-lookup gather
 // queue is cut for wavefronts that sum bags in matrix slots (gather-only fp32 plans, G 2 to 8).
+// G = 1 of a gather-only plan: two lanes per row, one in wave mode (16-byte rows).
 int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, bool slots, int grid,
                   int lds_bytes, void* stream);
 int launch_gather(const LookupArgs& a, int G, bool f16, bool weighted, int ks, int grid, int block, int lds_bytes,

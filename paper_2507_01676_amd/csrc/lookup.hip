@@ -1820,7 +1820,8 @@ struct Slots {
 // first copied into LDS (`lds`), so that finding a chunk's table and bags costs no
 // memory round trip.
 // SLOTS: the multi-lookup queue is cut for Slots (chunks per wavefront), not for SWs.
-template <int G, bool F16, bool W, bool SLOTS>
+// WAVE1: rows are 16 bytes, and in wave mode the lane that idles elsewhere is a SW of its own.
+template <int G, bool F16, bool W, bool SLOTS, bool WAVE1>
 __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, const Lane& l, int wg,
                                              LMEM int* qctr) {
   {   // the worker's slot: a header record, then its runs
@@ -1852,8 +1853,15 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
       const LMEM GatherRun& g = runs[s.e];
       f.w = as_global(static_cast<const char*>(g.w));
       f.rows = static_cast<uint64_t>(g.rows);
-      walk_wave<G, F16, W>(idx, offsets + static_cast<int64_t>(g.table) * a.B, s.bs, s.be,
-                           out + static_cast<int64_t>(g.table) * a.E, ost, l.lane_sw, l.sw_w, g.mean != 0, f);
+      if constexpr (WAVE1) {
+        f.lane_c = 0;
+        f.active = true;
+        walk_wave<1, F16, W>(idx, offsets + static_cast<int64_t>(g.table) * a.B, s.bs, s.be,
+                             out + static_cast<int64_t>(g.table) * a.E, ost, 0, l.tid & (kWave - 1), g.mean != 0, f);
+      } else {
+        walk_wave<G, F16, W>(idx, offsets + static_cast<int64_t>(g.table) * a.B, s.bs, s.be,
+                             out + static_cast<int64_t>(g.table) * a.E, ost, l.lane_sw, l.sw_w, g.mean != 0, f);
+      }
     }
   }
   {  // single-lookup bags
@@ -1878,7 +1886,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
 
 // STAGED = false: the plan has gather slices only (no LDS, no staged-slice code).
 // W: every lookup carries a weight (a.weights).
-template <int G, bool F16, bool STAGED, bool W, bool SLOTS>
+template <int G, bool F16, bool STAGED, bool W, bool SLOTS, bool WAVE1 = false>
 __global__ void __launch_bounds__(kBlock) lookup_kernel(LookupArgs a) {
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ int s_last;
@@ -1918,7 +1926,7 @@ __global__ void __launch_bounds__(kBlock) lookup_kernel(LookupArgs a) {
   }
   if (tw && l.tid == 0) tw[1] = now_ticks();
   __syncthreads();   // staged slices are done with LDS
-  gather_phase<G, F16, W, SLOTS>(a, (lchar*)smem_raw, l, wg, (LMEM int*)&s_queue);
+  gather_phase<G, F16, W, SLOTS, WAVE1>(a, (lchar*)smem_raw, l, wg, (LMEM int*)&s_queue);
   if (tw && (l.tid & (kWave - 1)) == 0) tw[2 + l.wave] = now_ticks();
 }
 
@@ -2014,9 +2022,10 @@ __global__ void __launch_bounds__(256) fill_kernel(char* dst, int64_t row_begin,
 
 using KernelFn = void (*)(LookupArgs);
 
-// gather-only kernels whose multi-lookup queue is cut for Slots
+// gather-only kernels whose multi-lookup queue is cut for Slots (G = 1: see pick)
 template <bool W>
 KernelFn pick_slots(int G) {
+  if (G == 1) return &lookup_kernel<2, false, false, W, true, true>;
   if (G == 2) return &lookup_kernel<2, false, false, W, true>;
   if (G == 4) return &lookup_kernel<4, false, false, W, true>;
   if (G == 8) return &lookup_kernel<8, false, false, W, true>;
@@ -2025,9 +2034,9 @@ KernelFn pick_slots(int G) {
 template <bool F16, bool STAGED, bool W>
 KernelFn pick(int G) {
   switch (G) {
-    case 1:   // staged plans only
+    case 1:   // gather-only plans: one lane per row in wave mode, two elsewhere
       if constexpr (STAGED) return &lookup_kernel<1, F16, true, W, false>;
-      return nullptr;
+      else return &lookup_kernel<2, F16, false, W, false, true>;
     case 2: return &lookup_kernel<2, F16, STAGED, W, false>;
     case 4: return &lookup_kernel<4, F16, STAGED, W, false>;
     case 8: return &lookup_kernel<8, F16, STAGED, W, false>;

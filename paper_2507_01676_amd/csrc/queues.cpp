@@ -27,8 +27,10 @@ bool gather_only(const PlanOut& P) {
 // kernels spilled 300-500 registers, and their scratch costs each launch several us.  One
 // lane against two: 8 tables of 4332 one-lookup fp16 bags 10.8 -> 5.0 us, 12 weighted tables
 // at batch 1 24.1 -> 13.4, 8M lookups in bags of 40 75.0 -> 72.3, 49.6 in fp32 (73.3); fp16
-// bags of 8, 1.6M lookups, 18.9 -> 20.5 (24.6 before matrix slots).  Staged plans keep one
-// lane: their LDS rows lose more by half the SWs (all-LDS fp32 8.3 -> 9.5 ms, HOT 62 -> 71 us).
+// bags of 8, 1.7M lookups, 26.2 -> 23.4; slower only for 1.7M bags of one lookup whose maximum
+// is not stated, 25.2 -> 28.4 and 32.0 -> 35.0 in fp16.  (Long bags: see wave_lanes.)  Staged
+// plans keep one lane: their LDS rows lose more by half the SWs (all-LDS fp32 8.3 -> 9.5 ms,
+// HOT 62 -> 71 us).
 int plan_lanes(const PlanOut& P) {
   return gather_only(P) ? std::max(2, lanes_per_row(P.R)) : lanes_per_row(P.R);
 }
@@ -88,6 +90,24 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       const double s_t = stats[d.table].mean_pooling;
       d.mode = (s_t >= 4.0 * (64 / G) && s_t * (kBlock / G) > Wg) ? 1 : 0;
     }
+  }
+
+  // Long bags of 16-byte rows are walked with one lane per row, 64 rows per load of a wavefront,
+  // where most of the wave-mode lookups are in bags of 256 or more (5000 lookups: 20.9 us on two
+  // lanes, 13.7 on one; 1000: 7.0 and 5.8; 300: 5.2 and 4.9; 9.75M lookups in bags of 150: 65 and
+  // 70).  These are kernels of their own: with both walkers in one, the two-lane bags of 100
+  // fp16 lookups ran 82.5 us instead of 72.5.
+  q->wave_lanes = G;
+  if (!staged && P.R <= 16) {
+    double in_wave = 0.0, in_long = 0.0;
+    for (const Item& d : items)
+      if (d.mode) {
+        const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
+        const double s_t = stats[d.table].mean_pooling;
+        in_wave += static_cast<double>(nb) * s_t;
+        if (s_t >= 256.0) in_long += static_cast<double>(nb) * s_t;
+      }
+    if (in_long > 0.0 && in_long >= 0.5 * in_wave) q->wave_lanes = 1;
   }
 
   // gather run queues per worker, slices in plan order: wave-mode runs, then runs of
@@ -233,7 +253,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   {
     const int nsw = kBlock / G;
     const int nwaves = block / 64;
-    const double wave_chunk = 4.0 * 8.0 * (64 / G);
+    const double wave_chunk = 4.0 * 8.0 * (64 / q->wave_lanes);
     auto slice_bags = [&](const Item& d) -> int64_t {
       return (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
     };
@@ -332,13 +352,13 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   return EMB_OK;
 }
 
-std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int ksteps, int slot,
+std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int wave_lanes, int ksteps, int slot,
                         const std::vector<GatherRun>& records) {
   static const char* const names[] = {"wave", "single", "multi"};
   char line[160];
-  std::snprintf(line, sizeof line, "kernel %s lanes %d walker %s steps %d\n",
+  std::snprintf(line, sizeof line, "kernel %s lanes %d walker %s steps %d wave_lanes %d\n",
                 wave_gather ? "gather_kernel" : "lookup_kernel", plan_lanes(P),
-                wave_gather ? "wavefront" : slots ? "slots" : "sw", ksteps);
+                wave_gather ? "wavefront" : slots ? "slots" : "sw", ksteps, wave_lanes);
   std::string s = line;
   for (int w = 0; w < P.K; ++w) {
     const GatherRun* const r = &records[static_cast<size_t>(w) * slot];

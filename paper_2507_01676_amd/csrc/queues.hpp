@@ -32,6 +32,7 @@ struct QueueIn {
 
 struct GatherQueues {
   bool slots = false;               // lookup_kernel sums multi-lookup bags in matrix slots
+  int wave_lanes = 0;               // lanes of a row in lookup_kernel's wave mode
   int ksteps = 0;                   // gather_kernel: row loads in flight per lane per step
   int slot = 1;                     // records per worker: a GatherSlotHeader, then its runs
   std::vector<GatherRun> records;   // [K * slot]; table pointers are set at bind
@@ -42,9 +43,9 @@ struct GatherQueues {
 // 0 on success, otherwise an emb_status_t code.
 int gather_queues(const QueueIn& in, GatherQueues* out);
 
-// One line of kernel, lanes, walker and steps, then one per run: worker, queue, table, batch
+// One line of kernel, lanes, walker, steps and lanes in wave mode, then one per run: worker, queue, table, batch
 // slice, slices, bags per chunk.
-std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int ksteps, int slot,
+std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int wave_lanes, int ksteps, int slot,
                         const std::vector<GatherRun>& records);
 
 }  // namespace embx

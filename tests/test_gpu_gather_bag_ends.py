@@ -165,3 +165,37 @@ def test_chunks_longer_than_the_rebase_distance(monkeypatch, E, dtype, pooling):
         else:   # a division by the length as a multiplication: two roundings of half an ulp
             assert OP.pooled_error(out.cpu().numpy(), ref, mag) <= 2.0 ** -22
         assert plan.check_errors() == bad
+
+
+@pytest.mark.parametrize("pooling", ["sum", "mean"])
+@pytest.mark.parametrize("E,dtype", [(4, "f32"), (8, "f16"), (8, "f32"), (16, "f16")])
+def test_long_bags_of_the_narrowest_rows(E, dtype, pooling):
+    """A wavefront per bag: 64 one-lane sub-wavefronts on 16-byte rows, 32 of two lanes on
+    32-byte ones; lengths around a round of them, a step of 8 rounds, and several steps."""
+    import torch
+
+    import paper_2507_01676_amd as embx
+    log(f"long bags, E{E} {dtype} {pooling}")
+    g = np.random.default_rng(13)
+    lens = np.array([511, 512, 513, 1, 0, 1024, 5000, 63, 64, 65, 31, 32, 33, 255, 256, 257, 0, 2049, 7, 1025])
+    rows, B = [7, 50_000, 900], lens.size
+    c = W.Config(172, "long bags", E, dtype, -1.0, 1.0, B, [W.TableSpec(m, "fixed", 1, 1, 1, "uniform") for m in rows])
+    c.value_seeds = [W.value_seed(172, t) for t in range(len(rows))]
+    off = np.zeros(len(rows) * B + 1, np.int64)
+    np.cumsum(np.concatenate([g.permutation(lens) for _ in rows]), out=off[1:])
+    n = off[::B]
+    idx = np.concatenate([g.integers(0, m, size=int(n[t + 1] - n[t])) for t, m in enumerate(rows)])
+    idx[g.random(idx.size) < 0.02] = -1
+    hw = host_tables(c, W.VAL_INTEGER)
+    plan = embx.Plan(rows, E, dtype, [{"mean_pooling": float(lens.mean()), "max_pooling": 0}] * 3, B, pooling=pooling,
+                     num_workers=3).bind(upload_tables(hw))
+    assert {ln.split()[1] for ln in plan.queues().splitlines()[1:]} == {"wave"}
+    d_idx, d_off = to_device(W.Batch(B, len(rows), idx, off))
+    for w in (None, g.integers(-3, 4, size=idx.size).astype(np.float32)):
+        out = torch.full((B, len(rows), E), float("nan"), device="cuda")
+        plan.lookup(d_idx, d_off, B, out, weights=None if w is None else torch.from_numpy(w).cuda())
+        torch.cuda.synchronize()
+        # sums of up to 5000 integers: exact below 2^24, which 64 partial sums stay under and the totals may not
+        ref, mag, bad = OP.pool_reference(hw, idx, off, B, psw=w, pooling=pooling)
+        assert OP.pooled_error(out.cpu().numpy(), ref, mag) <= 2.0 ** -20
+        assert plan.check_errors() == bad

@@ -63,3 +63,14 @@ def test_a_slots_chunk_fills_a_step(E, sws, most, bag):
             bags = {r[5] for r in runs if r[1] == "multi"}
             least = max(1, min(most, int(8 // max(1.0, bag))))
             assert bags <= {sws * m for m in range(least, most + 1)}, (batch, bags)
+
+
+@pytest.mark.parametrize("E,dtype,bytes_", [(4, "f32", 16), (8, "f16", 16), (8, "f32", 32), (16, "f16", 32)])
+def test_long_bags_of_16_byte_rows_take_one_lane(E, dtype, bytes_):
+    for bag in (150.0, 255.0, 256.0, 5000.0):
+        rows, stats = tables(4, bag)
+        head, runs = queues(rows, E, dtype, stats, 8)
+        assert {r[1] for r in runs} == {"wave"} and head["lanes"] == "2"
+        assert head["wave_lanes"] == ("1" if bytes_ == 16 and bag >= 256 else "2")
+    rows, stats = tables(26, 8.0)
+    assert queues(rows, E, dtype, stats, 8192)[0]["wave_lanes"] == "2"
