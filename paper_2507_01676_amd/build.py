@@ -47,10 +47,10 @@ def _run(cmd, verbose):
     return r
 
 
-# lookup.hip is compiled in parts (EMBX_PART): one per (row type, weighted) kernel
-# family, plus the probes, filler and launch code, plus one per fp32 family of gather-only
-# kernels with wave-uniform control
-LOOKUP_PARTS = 7
+# lookup.hip is compiled in parts (EMBX_PART): one per (row type, weighted) kernel family of
+# staged plans and of gather-only ones, plus the probes, filler and launch code, plus one per
+# fp32 family of gather-only kernels with wave-uniform control
+LOOKUP_PARTS = 11
 LOOKUP_UNIFORM_PARTS = (5, 6)
 # gather.hip: one part per (row type, weighted) kernel family, each built for every number
 # of row loads in flight per step a plan may choose (kGatherStepChoices in device_types.hpp)

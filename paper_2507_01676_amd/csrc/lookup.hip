@@ -46,10 +46,10 @@
 #include "device_types.hpp"
 
 // The lookup kernels are compiled in parts so that a build can run the parts in
-// parallel: EMBX_PART 0..3 holds the kernels of one (row type, weighted) pair, part 4
-// the probes, the table filler and the launch code, parts 5 and 6 the fp32 kernels of
-// gather-only plans with rows in matrix slots (their control is wave-uniform, see
-// build.py).  Without EMBX_PART one compile holds everything.
+// parallel: EMBX_PART 0..3 holds the kernels of plans with staged slices of one (row type,
+// weighted) pair, 7..10 those of gather-only plans, part 4 the probes, the table filler and
+// the launch code, parts 5 and 6 the fp32 kernels of gather-only plans with rows in matrix
+// slots (their control is wave-uniform, see build.py).  Without EMBX_PART one compile holds everything.
 #ifndef EMBX_PART
 #define EMBX_PART -1
 #endif
@@ -345,15 +345,6 @@ __device__ __forceinline__ int sw_bcast(int v) {
     return __builtin_amdgcn_update_dpp(lo, v, 0x158 + U, 0xF, 0xC, false);
   }
 }
-// The same for the SW walkers, of any G.  They are bound by the vector unit, so from 8 lanes
-// on, where DPP takes two instructions, they shuffle through LDS (0.26M bags of 4 lookups of
-// 128-byte fp16 rows: 323 us, 348 with DPP).
-template <int G, int U>
-__device__ __forceinline__ int sw_share(int v) {
-  if constexpr (G <= 4) return sw_bcast<G, U>(v);
-  else return __shfl(v, U, G);
-}
-
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -362,6 +353,52 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// The SW walkers of gather-only kernels (parts 7 on) share by DPP where that is one instruction,
+// G <= 4; the others shuffle through LDS.  The walkers are bound by the vector unit (1M bags of 4
+// lookups of 128-byte fp16 rows: 323 us, 348 with DPP's two instructions), and the kernels with
+// staged flows spill: loops unrolled over immediates cost them registers (LDS chunks of 64-byte
+// rows 3400 -> 3900 us, HOT on 128-byte rows 28.3 -> 30.6, on 256-byte rows 28.1 -> 29.5), and so
+// does a function around the shuffle.
+//   EMBX_FOR_LOOKUPS(u) { body } EMBX_END_LOOKUPS;   for each lookup u of a step
+//   EMBX_SHARE(mine, u)                              lane u % G's mine[u / G]
+#if EMBX_PART >= 5
+template <int G, class F>
+__device__ __forceinline__ void for_lookups(F&& f) {
+  if constexpr (G <= 4) {
+    static_for<kU>(f);
+  } else {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) f(u);
+  }
+}
+template <int G, class T, class U>
+__device__ __forceinline__ T sw_share(const T& v, U u) {
+  static_assert(sizeof(T) == 4, "");
+  if constexpr (G > 4) return __shfl(v, u % G, G);
+  else return __builtin_bit_cast(T, sw_bcast<G, U::value % G>(__builtin_bit_cast(int, v)));
+}
+#define EMBX_FOR_LOOKUPS(u) for_lookups<G>([&](auto u) __attribute__((always_inline))
+#define EMBX_END_LOOKUPS )
+#define EMBX_SHARE(mine, u) sw_share<G>(mine[u / G], u)
+#else
+#define EMBX_FOR_LOOKUPS(u) _Pragma("unroll") for (int u = 0; u < kU; ++u)
+#define EMBX_END_LOOKUPS
+#define EMBX_SHARE(mine, u) (G == 1 ? mine[u] : __shfl(mine[u / G], u % G, G))
+#endif
+template <int G, int N, class U>
+__device__ __forceinline__ int64_t share64(const int64_t (&mine)[N], U u) {
+  int64_t v = mine[u / G];
+  if constexpr (G > 1) {
+#if EMBX_PART >= 5
+    const int lo = sw_share<G>(static_cast<int>(v & 0xffffffff), u), hi = sw_share<G>(static_cast<int>(v >> 32), u);
+#else
+    const int lo = __shfl(static_cast<int>(v & 0xffffffff), u % G, G), hi = __shfl(static_cast<int>(v >> 32), u % G, G);
+#endif
+    v = (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
+  }
+  return v;
 }
 
 // The kU upcoming lookups of a SW are loaded one per lane (IPL per lane when the SW
@@ -405,7 +442,7 @@ struct Ids {
       mine[j] = (in_range && ok) ? static_cast<int32_t>(raw[j]) : -1;
       if (in_range && !ok) f.bad();
     }
-    static_for<kU>([&](auto u) __attribute__((always_inline)) { ix[u] = sw_share<G, u % G>(mine[u / G]); });
+    EMBX_FOR_LOOKUPS(u) { ix[u] = EMBX_SHARE(mine, u); } EMBX_END_LOOKUPS;
   }
 
   // The row address of each of the kU lookups, for this lane's 16 bytes of the row:
@@ -421,19 +458,14 @@ struct Ids {
       if (in_range && !ok) f.bad();
       mine[j] = reinterpret_cast<int64_t>(in_range && ok ? f.w + raw[j] * f.R : f.zero);
     }
-    static_for<kU>([&](auto u) __attribute__((always_inline)) {
-      const int64_t v = mine[u / G];
-      const int lo = sw_share<G, u % G>(static_cast<int>(v & 0xffffffff));
-      const int hi = sw_share<G, u % G>(static_cast<int>(v >> 32));
-      a[u] = reinterpret_cast<gchar*>((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo)) + f.lane_c;
-    });
+    EMBX_FOR_LOOKUPS(u) { a[u] = reinterpret_cast<gchar*>(share64<G>(mine, u)) + f.lane_c; } EMBX_END_LOOKUPS;
   }
 
   // the weight of each of the kU lookups (the run-time 1 without weights)
   __device__ __forceinline__ void weights(const RowBase& f, float (&wt)[kU]) const {
     float mine[W ? IPL : 1];
     own_weights(f, mine);
-    static_for<kU>([&](auto u) __attribute__((always_inline)) { wt[u] = weight_of<u>(f, mine); });
+    EMBX_FOR_LOOKUPS(u) { wt[u] = weight_of(f, mine, u); } EMBX_END_LOOKUPS;
   }
   // the weights of this lane's own positions (0 past the end or for an invalid id) ...
   __device__ __forceinline__ void own_weights(const RowBase& f, float (&mine)[W ? IPL : 1]) const {
@@ -447,10 +479,10 @@ struct Ids {
     }
   }
   // ... and position u's weight, shared within the SW when it is used
-  template <int U>
-  static __device__ __forceinline__ float weight_of(const RowBase& f, const float (&mine)[W ? IPL : 1]) {
+  template <class U>
+  static __device__ __forceinline__ float weight_of(const RowBase& f, const float (&mine)[W ? IPL : 1], U u) {
     if constexpr (!W) return f.one;
-    else return __int_as_float(sw_share<G, U % G>(__float_as_int(mine[U / G])));
+    else return EMBX_SHARE(mine, u);
   }
 };
 
@@ -1290,7 +1322,7 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
       // (a lane outside the row stores nothing and keeps no output pointer: its bag
       // count b follows from m alone)
       const uint32_t fs = f.active ? fm : 0u;
-      static_for<kU>([&](auto u) __attribute__((always_inline)) {   // lookups past the end read the zero row
+      EMBX_FOR_LOOKUPS(u) {   // lookups past the end read the zero row
         if ((fs >> u) & 1u) {
           if (mean) acc_mean(acc, p + u - bstart);
           bstart = p + u;
@@ -1298,13 +1330,13 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
           acc_zero(acc);
           obb += ostride;
         }
-        acc_add(acc, raw[u], Ids<G, W>::template weight_of<u>(f, wm));
-      });
+        acc_add(acc, raw[u], Ids<G, W>::weight_of(f, wm, u));
+      } EMBX_END_LOOKUPS;
       b += m;
     } else {
       wait_all();
       int64_t e = off[min(b + 1, be)];   // end of bag b
-      static_for<kU>([&](auto u) __attribute__((always_inline)) {
+      EMBX_FOR_LOOKUPS(u) {
         while (u < n && e == p + u) {
           if (mean) acc_mean(acc, e - bstart);
           bstart = e;
@@ -1314,8 +1346,8 @@ __device__ __forceinline__ void walk_stream(GMEM const int64_t* __restrict__ ind
           obb += ostride;
           e = off[min(b + 1, be)];
         }
-        acc_add(acc, raw[u], Ids<G, W>::template weight_of<u>(f, wm));
-      });
+        acc_add(acc, raw[u], Ids<G, W>::weight_of(f, wm, u));
+      } EMBX_END_LOOKUPS;
       win = off[min(b + 1 + lane_sw, be)];
       wait_all();
     }
@@ -1451,15 +1483,9 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
       multi = multi || h0.en[j] - h0.st[j] > 1;
     }
     uint4 raw[kU];
-    static_for<kU>([&](auto u) __attribute__((always_inline)) {
-      const int lo = sw_share<G, u % G>(static_cast<int>(addr[u / G] & 0xffffffff));
-      const int hi = sw_share<G, u % G>(static_cast<int>(addr[u / G] >> 32));
-      raw[u] = ldg16(reinterpret_cast<gchar*>((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo)) + f.lane_c);
-    });
+    EMBX_FOR_LOOKUPS(u) { raw[u] = ldg16(reinterpret_cast<gchar*>(share64<G>(addr, u)) + f.lane_c); } EMBX_END_LOOKUPS;
     float wt[kU];
-    static_for<kU>([&](auto u) __attribute__((always_inline)) {
-      wt[u] = W ? __int_as_float(sw_share<G, u % G>(__float_as_int(wm[u / G]))) : 0.0f;
-    });
+    EMBX_FOR_LOOKUPS(u) { wt[u] = !W ? 0.0f : EMBX_SHARE(wm, u); } EMBX_END_LOOKUPS;
     wait_all();   // the one wait of the step
     const int nb = cur.be - cur.bs;
 #pragma unroll
@@ -2052,32 +2078,40 @@ KernelFn pick(int G) {
 // The kernel for rows of G lanes, one per (row type, weighted) pair, each defined in
 // its own part.
 using LookupKernelFn = void (*)(LookupArgs);
-LookupKernelFn lookup_kernel_f32(int G, bool staged);
-LookupKernelFn lookup_kernel_f32_weighted(int G, bool staged);
-LookupKernelFn lookup_kernel_f16(int G, bool staged);
-LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged);
+LookupKernelFn staged_kernel_f32(int G);
+LookupKernelFn staged_kernel_f32_weighted(int G);
+LookupKernelFn staged_kernel_f16(int G);
+LookupKernelFn staged_kernel_f16_weighted(int G);
+LookupKernelFn gather_only_kernel_f32(int G);
+LookupKernelFn gather_only_kernel_f32_weighted(int G);
+LookupKernelFn gather_only_kernel_f16(int G);
+LookupKernelFn gather_only_kernel_f16_weighted(int G);
 LookupKernelFn slots_kernel_f32(int G);
 LookupKernelFn slots_kernel_f32_weighted(int G);
 
 #if EMBX_HAS_PART(0)
-LookupKernelFn lookup_kernel_f32(int G, bool staged) {
-  return staged ? pick<false, true, false>(G) : pick<false, false, false>(G);
-}
+LookupKernelFn staged_kernel_f32(int G) { return pick<false, true, false>(G); }
 #endif
 #if EMBX_HAS_PART(1)
-LookupKernelFn lookup_kernel_f32_weighted(int G, bool staged) {
-  return staged ? pick<false, true, true>(G) : pick<false, false, true>(G);
-}
+LookupKernelFn staged_kernel_f32_weighted(int G) { return pick<false, true, true>(G); }
 #endif
 #if EMBX_HAS_PART(2)
-LookupKernelFn lookup_kernel_f16(int G, bool staged) {
-  return staged ? pick<true, true, false>(G) : pick<true, false, false>(G);
-}
+LookupKernelFn staged_kernel_f16(int G) { return pick<true, true, false>(G); }
 #endif
 #if EMBX_HAS_PART(3)
-LookupKernelFn lookup_kernel_f16_weighted(int G, bool staged) {
-  return staged ? pick<true, true, true>(G) : pick<true, false, true>(G);
-}
+LookupKernelFn staged_kernel_f16_weighted(int G) { return pick<true, true, true>(G); }
+#endif
+#if EMBX_HAS_PART(7)
+LookupKernelFn gather_only_kernel_f32(int G) { return pick<false, false, false>(G); }
+#endif
+#if EMBX_HAS_PART(8)
+LookupKernelFn gather_only_kernel_f32_weighted(int G) { return pick<false, false, true>(G); }
+#endif
+#if EMBX_HAS_PART(9)
+LookupKernelFn gather_only_kernel_f16(int G) { return pick<true, false, false>(G); }
+#endif
+#if EMBX_HAS_PART(10)
+LookupKernelFn gather_only_kernel_f16_weighted(int G) { return pick<true, false, true>(G); }
 #endif
 
 #if EMBX_HAS_PART(5)
@@ -2091,8 +2125,12 @@ namespace {
 
 LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted, bool slots) {
   if (slots) return f16 || staged ? nullptr : weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
-  if (f16) return weighted ? lookup_kernel_f16_weighted(G, staged) : lookup_kernel_f16(G, staged);
-  return weighted ? lookup_kernel_f32_weighted(G, staged) : lookup_kernel_f32(G, staged);
+  if (staged) {
+    if (f16) return weighted ? staged_kernel_f16_weighted(G) : staged_kernel_f16(G);
+    return weighted ? staged_kernel_f32_weighted(G) : staged_kernel_f32(G);
+  }
+  if (f16) return weighted ? gather_only_kernel_f16_weighted(G) : gather_only_kernel_f16(G);
+  return weighted ? gather_only_kernel_f32_weighted(G) : gather_only_kernel_f32(G);
 }
 
 GatherKernelFn pick_gather_any(int G, bool f16, bool weighted, int ks) {
