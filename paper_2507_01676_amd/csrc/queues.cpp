@@ -49,7 +49,11 @@ namespace {
 // a slice of the plan, as far as the queues go
 struct Item {
   int32_t table, strat, j, k;
-  int32_t mode;   // gather: 1 = a wavefront per bag
+  int32_t mode;     // gather: 1 = a wavefront per bag
+  int64_t bags;     // at the max batch
+  double lookups;   // at the max batch, one per bag at least (divided out once: the rules below
+                    // pass over the slices about ten times)
+  bool multi;       // gather: more than one lookup per bag may occur
 };
 
 }  // namespace
@@ -70,7 +74,9 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   std::vector<int32_t> wg_ptr(K + 1, 0);
   items.reserve(P.slices.size());
   for (const PSlice& x : P.slices) {
-    items.push_back(Item{x.t, x.strat, x.j, x.k, 0});
+    const int64_t bags = (static_cast<int64_t>(x.j + 1) * max_batch) / x.k - (static_cast<int64_t>(x.j) * max_batch) / x.k;
+    items.push_back(Item{x.t, x.strat, x.j, x.k, 0, bags, static_cast<double>(bags) * std::max(1.0, stats[x.t].mean_pooling),
+                         x.strat == S_GATHER && stats[x.t].max_pooling != 1});
     wg_ptr[x.wg + 1] += 1;
   }
   for (int w = 0; w < K; ++w) wg_ptr[w + 1] += wg_ptr[w];
@@ -81,8 +87,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
       const Item& d = items[i];
       if (d.strat != S_GATHER) continue;
-      const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
-      Wg += static_cast<double>(nb) * std::max(1.0, stats[d.table].mean_pooling);
+      Wg += d.lookups;
     }
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
       Item& d = items[i];
@@ -102,10 +107,8 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     double in_wave = 0.0, in_long = 0.0;
     for (const Item& d : items)
       if (d.mode) {
-        const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
-        const double s_t = stats[d.table].mean_pooling;
-        in_wave += static_cast<double>(nb) * s_t;
-        if (s_t >= 256.0) in_long += static_cast<double>(nb) * s_t;
+        in_wave += d.lookups;
+        if (stats[d.table].mean_pooling >= 256.0) in_long += d.lookups;
       }
     if (in_long > 0.0 && in_long >= 0.5 * in_wave) q->wave_lanes = 1;
   }
@@ -147,19 +150,13 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   // 256-byte rows 108.9 -> 107.5 us; half or twice the share: within 2% of it.
   std::vector<int32_t> item_cb(items.size(), 1);
   // (lookup_kernel's wave-mode slices have a queue of their own)
-  auto multi_lookup = [&](const Item& d) {
-    return d.strat == S_GATHER && stats[d.table].max_pooling != 1 && (wave_gather || !d.mode);
-  };
+  auto multi_lookup = [&](const Item& d) { return d.multi && (wave_gather || !d.mode); };
   auto bag_lookups = [&](const Item& d) { return std::max(1.0, stats[d.table].mean_pooling); };
-  auto slice_lookups = [&](const Item& d) {
-    const int64_t nb = (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
-    return static_cast<double>(nb) * bag_lookups(d);
-  };
   auto wave_chunks = [&](int w, double N) {
     const int nwaves = block / 64;
     double W = 0.0;
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
-      if (multi_lookup(items[i])) W += slice_lookups(items[i]);
+      if (multi_lookup(items[i])) W += items[i].lookups;
     const double cap = std::max(2.0 * N, W / nwaves >= 64.0 * 192.0 ? 192.0 : 128.0);
     const double least = std::min(0.5 * N, W / nwaves);
     double left = W;
@@ -169,7 +166,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       const double target = wave_chunk_override > 0.0 ? wave_chunk_override
                                                       : std::min(cap, std::max(least, left / nwaves));
       item_cb[i] = static_cast<int32_t>(std::min(64.0, std::max(1.0, std::floor(target / bag_lookups(d)))));
-      left -= slice_lookups(d);
+      left -= d.lookups;
     }
   };
   // Narrow fp32 rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one
@@ -186,7 +183,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     double bags = 0.0, lookups = 0.0, filled = 0.0;
     for (const Item& d : items)
       if (multi_lookup(d)) {
-        const double n = slice_lookups(d), nb = n / bag_lookups(d);
+        const double n = d.lookups, nb = n / bag_lookups(d);
         bags += nb;
         lookups += n;
         filled += n * std::min(1.0, nb / S);
@@ -204,14 +201,14 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     const int S = 64 / G, M = std::min(4, G), nwaves = block / 64;
     double left = 0.0;
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i)
-      if (multi_lookup(items[i])) left += slice_lookups(items[i]);
+      if (multi_lookup(items[i])) left += items[i].lookups;
     for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
       const Item& d = items[i];
       if (!multi_lookup(d)) continue;
       const double share = std::floor(left / (nwaves * S * bag_lookups(d)));
       const double step = std::max(1.0, std::floor(kSlotStep / bag_lookups(d)));
       item_cb[i] = S * static_cast<int32_t>(std::min(static_cast<double>(M), std::max(step, share)));
-      left -= slice_lookups(d);
+      left -= d.lookups;
     }
   };
   if (wave_gather) {
@@ -254,9 +251,6 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
     const int nsw = kBlock / G;
     const int nwaves = block / 64;
     const double wave_chunk = 4.0 * 8.0 * (64 / q->wave_lanes);
-    auto slice_bags = [&](const Item& d) -> int64_t {
-      return (static_cast<int64_t>(d.j + 1) * max_batch) / d.k - (static_cast<int64_t>(d.j) * max_batch) / d.k;
-    };
     // Slice j of k holds floor((j+1)B/k) - floor(jB/k) bags at the runtime batch B, which
     // for some B < max_batch is one more than at max_batch (e.g. k = 256, j = 10: 3 bags at
     // B = 1000, 4 at B = 792).  Every B <= max_batch gives at most ceil(max_batch / k), so a
@@ -276,7 +270,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       };
       for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
         if (items[i].strat != S_GATHER) continue;
-        const double lk = static_cast<double>(slice_bags(items[i])) * std::max(1.0, stats[items[i].table].mean_pooling);
+        const double lk = items[i].lookups;
         const int cls = class_of(items[i]);
         if (cls == 0)
           Ww += lk;
