@@ -64,7 +64,8 @@ DEFAULT_CONFIG = 5
 KERNEL_SOURCES = ["paper_2507_01676_amd/csrc/lookup.hip", "paper_2507_01676_amd/csrc/gather.hip",
                   "paper_2507_01676_amd/csrc/device_types.hpp",
                   "paper_2507_01676_amd/csrc/planner.cpp", "paper_2507_01676_amd/csrc/planner.hpp",
-                  "paper_2507_01676_amd/csrc/api.cpp"]
+                  "paper_2507_01676_amd/csrc/api.cpp", "paper_2507_01676_amd/csrc/queues.cpp",
+                  "paper_2507_01676_amd/csrc/queues.hpp", "paper_2507_01676_amd/csrc/positions.hpp"]
 
 
 def log(msg):

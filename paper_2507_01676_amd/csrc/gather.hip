@@ -10,10 +10,12 @@
 // at that occupancy beats 6 or 8 at two workgroups per CU).  The file is built once per
 // kSteps (EMBX_GKS = 12, 13, 16) and a plan picks the one whose steps its chunks fill best.
 //
-// What bounds it: instruction issue on short bags, the vector memory pipe on long ones (at
-// 131M lookups of 512-byte rows its address unit is busy 88% of the time), and HBM writes
-// of the pooled rows (without them, 3.4M fp16 lookups of 256 bytes would take 64 us, not
-// 105).  Hence scalar control that costs three instructions per row load (see Multi).
+// What bounds it: instruction issue on short bags; on long ones the bytes beyond L2 (131M
+// lookups of 512-byte rows: 18.8 GB at 97% of a copy's rate, 3.80 ms) and close behind them the
+// vector memory pipe (its address unit is busy 88% of that time; with every row an L2 hit the
+// batch takes 2.84 ms); and HBM writes of the pooled rows (without them, 3.4M fp16 lookups of
+// 256 bytes would take 64 us, not 105).  Hence scalar control that costs three instructions per
+// row load (see Multi).
 //
 // A wavefront is S = 64 / G sub-wavefronts (SWs) of G lanes; lane i of a SW covers bytes
 // [16 i, 16 i + 16) of a row.  A step covers N = S * kSteps consecutive lookups of the

@@ -30,8 +30,9 @@
 //          three queues of small chunks: long bags (wave mode), bags of at most
 //          one lookup (a chunk of kU bags is one SW step and each row is its
 //          bag's output), and the rest (SW mode, walked as one stream across
-//          chunks; narrow rows by wavefronts in matrix slots, see Slots).  Invalid ids read a row of zeros; fp16 halves are added with
-//          a mixed-precision fma.
+//          chunks; narrow fp32 rows by wavefronts in matrix slots, see Slots).
+//          Invalid ids read a row of zeros; fp16 halves are added with a
+//          mixed-precision fma.
 //
 // All pointers carry their address space (1 = global, 3 = LDS) so that every
 // access compiles to a global_* or ds_* instruction, never a flat one.
@@ -49,7 +50,8 @@
 // parallel: EMBX_PART 0..3 holds the kernels of plans with staged slices of one (row type,
 // weighted) pair, 7..10 those of gather-only plans, part 4 the probes, the table filler and
 // the launch code, parts 5 and 6 the fp32 kernels of gather-only plans with rows in matrix
-// slots (their control is wave-uniform, see build.py).  Without EMBX_PART one compile holds everything.
+// slots (their control is wave-uniform, see build.py).  Without EMBX_PART one compile holds
+// everything.
 #ifndef EMBX_PART
 #define EMBX_PART -1
 #endif
@@ -1526,7 +1528,7 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
 
 // ---------------------------------------------------------------- gather: narrow rows in matrix slots
 //
-// Rows of 32 to 128 bytes, where the plan says so.  A wavefront takes a chunk of bags of one table,
+// fp32 rows of 16 to 128 bytes, where the plan says so.  A wavefront takes a chunk of bags of one table,
 // M = min(4, G) slots per SW: SW s of the S = 64 / G sums m' <= M consecutive bags, so the S
 // SWs walk S streams of lookups side by side and a row load covers S rows through one
 // descriptor.  v_mfma_f32_4x4x1 does the sums: it multiplies 16 blocks of 4 lanes, each D[4][4]
@@ -1541,14 +1543,15 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
 // frequent row holds a NaN (half of the bags): 24.9, 25.3 and 40.3 us on 32-, 64- and 128-byte
 // rows (finite: 18.6, 20.2, 26.2; by SWs 21.9, 26.1, 35.8; again bag by bag, without loads in
 // flight: 36.6, 48.0, 86.0); a NaN in a rare row 20.1, 22.1, 29.2.
-// G < 4: a block holds 4 / G SWs, and a lane uses the part of D whose slots are its own SW's.
+// G = 2: a block holds two SWs, and a lane uses the part of D whose slots are its own SW's.
 //
 // What bounds it: the 128-byte lines beyond L2 (57 G/s on this device at any row size) on
 // large batches, the chain of offsets, ids and rows on small ones.  Before, each SW walked its
-// own stream of one table, with addresses shared by LDS shuffles and a masked store per
-// lookup: 68 vector instructions per row load, here 11 and 4 matrix instructions (fp32).  Bags
-// of 8 of 64-byte rows: 1.6M lookups 25.0 -> 18.1 us, 13.6M 156 -> 142 us; 128-byte rows 34.1
-// -> 25.2 us, bags of 20 59.2 -> 48.8 us, of 60 128 -> 122 us, of 2 23.0 -> 14.4 us.
+// own stream of one table, with addresses shared by LDS shuffles and a masked store per lookup.
+// Counted on 1.6M lookups of 64-byte rows in bags of 8 (millions of wavefront instructions): vector
+// 6.90 -> 4.35, of which 0.81 matrix ones, scalar 4.63 -> 1.78, LDS 0.69 -> 0.09.  Bags of 8 of
+// 64-byte rows: 1.6M lookups 25.0 -> 18.1 us, 13.6M 156 -> 142 us; 128-byte rows 34.1 -> 25.2 us,
+// bags of 20 59.2 -> 48.8 us, of 60 128 -> 122 us, of 2 23.0 -> 14.4 us.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 }  // namespace
 // structured buffer load of 16 bytes: base + vindex * stride + voffset, zeros where vindex >= num_records
@@ -1572,7 +1575,7 @@ struct Slots {
   static_assert(G == 2 || G == 4 || G == 8, "whole SWs per block of 4 lanes, or whole blocks per SW");
   static constexpr int S = kWave / G, M = G < 4 ? G : 4;
   static constexpr int NA = 4;
-  static constexpr int kUS = kSlotStep;       // rows in flight per SW (16 spill registers)
+  static constexpr int kUS = kSlotStep;       // rows in flight per SW
   static constexpr int IPL = kUS / G;         // ids per lane of a step: lane c holds lookups c, c + G, ...
 
   struct Chunk {   // bags [c0, c1) of run `run` (-1: none), and this lane's slot of it

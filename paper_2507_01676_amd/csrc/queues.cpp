@@ -115,18 +115,20 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
 
   // gather run queues per worker, slices in plan order: wave-mode runs, then runs of
   // tables whose bags hold at most one lookup (kChunkSingle bags per chunk: one step
-  // of a SW), then SW-mode runs.  SW-mode chunks carry about sqrt(5 W / NSW) expected
-  // lookups (W: the worker's SW-mode lookups at the max batch), at least one full step
-  // (8) and at most 128; wave-mode chunks carry about four wavefront steps of lookups,
-  // fewer when that leaves some of the 16 wavefronts without one.
+  // of a SW), then the other runs.  Of these, chunks that SWs walk carry about sqrt(5 W / NSW)
+  // expected lookups (W: the worker's lookups in this queue at the max batch), at least one full
+  // step (8) and at most 128; chunks for matrix slots see narrow_chunks.  Wave-mode chunks carry
+  // about four wavefront steps of lookups, fewer when that leaves some of the 16 wavefronts
+  // without one.
   //
   // The wave-uniform gather kernel's queues are single-lookup bags (chunks of one wavefront
-  // step: ksteps S bags) and all other bags, in chunks of about 128 expected lookups, 192 when
-  // the worker's queue gives each wavefront at least 64 chunks (W / 16 >= 64 * 192, W the
-  // worker's lookups in that queue), and at least two wavefront steps (EMBX_WAVE_CHUNK
-  // overrides it).  Measured on workloads 3-5: shorter chunks keep a worker's wavefronts
-  // on fewer tables at a time, so their rows share L2; much shorter ones pay the per-chunk
-  // start (workload 5: 4358 us at 64 lookups, 4042 at 192, 4170 at 512).
+  // step: ksteps S bags) and all other bags, in chunks of a wavefront's share of what is left
+  // (wave_chunks): from half a step to 128 expected lookups, 192 when the worker's queue gives
+  // each wavefront at least 64 chunks (W / 16 >= 64 * 192), or two steps if that is more, and
+  // at most 64 bags (EMBX_WAVE_CHUNK overrides the share).  The cap, measured on workload 5
+  // when every chunk had its size: 4358 us at 64 lookups, 4042 at 192, 4170 at 512 -- shorter
+  // chunks keep a worker's wavefronts on fewer tables at a time, so their rows share L2; much
+  // shorter ones pay the per-chunk start.
   const char* env_chunk = std::getenv("EMBX_WAVE_CHUNK");
   const double wave_chunk_override = env_chunk ? std::atof(env_chunk) : 0.0;
   // Rows in flight per step of the wave-uniform gather kernel (one build per choice): the
@@ -146,7 +148,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
   // chunks; not below half a step (or the share of the whole queue), where a chunk's start
   // costs more than it evens out, nor above the cap described above; at most 64 bags, the bag
   // ends a wavefront holds.  Measured against the cap alone: 60k lookups of 1-KB rows (15 per
-  // wavefront) 19.5 -> 12.6 us, 72k lookups of 384-byte rows 34.2 -> 33.6 us, 3.4M lookups of
+  // wavefront) 19.5 -> 12.6 us, 717k lookups of 384-byte rows 34.2 -> 33.6 us, 3.4M lookups of
   // 256-byte rows 108.9 -> 107.5 us; half or twice the share: within 2% of it.
   std::vector<int32_t> item_cb(items.size(), 1);
   // (lookup_kernel's wave-mode slices have a queue of their own)
