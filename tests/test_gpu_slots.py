@@ -189,3 +189,13 @@ def test_beside_a_single_lookup_queue(E):
         ref, _, bad = OP.pool_reference(hw, idx, off, B, psw=w)
         assert np.array_equal(got, ref)
         assert plan.check_errors() == bad
+
+
+@pytest.mark.parametrize("E,dtype", [(4, "f32"), (16, "f32"), (32, "f16"), (128, "f32")])
+def test_a_plan_has_the_queues_of_the_host_text(E, dtype):
+    import paper_2507_01676_amd as embx
+    log(f"queues of a device plan, E{E} {dtype}")
+    rows = [1000 + 40 * t for t in range(12)]
+    stats = [{"mean_pooling": m, "max_pooling": 1 if m == 1.0 else 0} for m in (1.0, 3.0, 8.0, 700.0) * 3]
+    plan = embx.Plan(rows, E, dtype, stats, 2000, num_workers=64)
+    assert plan.queues() == embx.queue_text(rows, E, dtype, stats, 2000, 64)
