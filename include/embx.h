@@ -293,9 +293,11 @@ emb_status_t emb_debug_check_input(const emb_plan_t* plan, const int64_t* indice
 
 /* ---- run queues (tests of the kernel choice and of the work's division) -----------------
  * Text of the gather slices as the kernels walk them: a line "kernel <name> lanes <n> walker
- * <wavefront | slots | sw> steps <n> wave_lanes <n>" (walker: gather_kernel's wavefronts;
- * lookup_kernel's matrix slots or sub-wavefronts; wave_lanes: a row's lanes in the wave queue), then one line per run of a worker's queues: worker, queue
- * (wave, single or multi), table, batch slice, slices, bags per chunk.  Written as
+ * <wavefront | slots | sw> weighted <walker> steps <n> wave_lanes <n>" (walker: gather_kernel's
+ * wavefronts; lookup_kernel's matrix slots or sub-wavefronts; weighted: of weighted lookups of at
+ * least half the max batch; wave_lanes: a row's lanes in the wave queue), then one line per run of a worker's queues: worker, queue
+ * (wave, single or multi), table, batch slice, slices, bags per chunk, bags per chunk of matrix
+ * slots (0: none).  Written as
  * emb_plan_serialize writes.  emb_debug_queue_text is host only: the plan that emb_plan_text
  * makes, on a device with 160 KiB of LDS per workgroup. */
 emb_status_t emb_debug_queue_text(int32_t num_tables, const int64_t* rows, int32_t embedding_dim,

@@ -49,9 +49,9 @@ def _run(cmd, verbose):
 
 # lookup.hip is compiled in parts (EMBX_PART): one per (row type, weighted) kernel family of
 # staged plans and of gather-only ones, plus the probes, filler and launch code, plus one per
-# fp32 family of gather-only kernels with wave-uniform control
-LOOKUP_PARTS = 11
-LOOKUP_UNIFORM_PARTS = (5, 6)
+# family of gather-only kernels with wave-uniform control
+LOOKUP_PARTS = 12
+LOOKUP_UNIFORM_PARTS = (5, 6, 11)
 # gather.hip: one part per (row type, weighted) kernel family, each built for every number
 # of row loads in flight per step a plan may choose (kGatherStepChoices in device_types.hpp)
 GATHER_PARTS = 4

@@ -50,7 +50,7 @@ struct emb_plan {
   GatherRun* d_gr = nullptr;
   const char* d_zero_row = nullptr;      // R zero bytes
   bool staged = false;                   // the plan has LDS / HOT / DEDUP / STREAM slices
-  bool slots = false;                    // lookup_kernel sums multi-lookup gather bags in matrix slots
+  bool slots = false;                    // launches may sum multi-lookup gather bags in matrix slots
   int wave_lanes = 0;                    // lanes of a row in lookup_kernel's wave mode
   bool wave_gather = false;              // launches the wave-uniform gather kernel (gather.hip)
   int block = kBlock;                    // threads per worker
@@ -702,8 +702,9 @@ emb_status_t lookup_impl(emb_plan_t* plan, const int64_t* indices, const int64_t
     return st(launch_gather(a, plan->G, plan->f16, weighted, plan->ksteps, plan->K, plan->block, plan->lds_bytes,
                             stream));
   // (G = 1 of a gather-only plan: the kernels whose wave mode takes one lane per row)
-  return st(launch_lookup(a, plan->wave_lanes == 1 ? 1 : plan->G, plan->f16, plan->staged, weighted, plan->slots,
-                          plan->K, plan->lds_bytes, stream));
+  const bool slots = launch_slots(plan->slots, plan->f16, weighted, batch, plan->Bmax);
+  return st(launch_lookup(a, plan->wave_lanes == 1 ? 1 : plan->G, plan->f16, plan->staged, weighted, slots, plan->K,
+                          plan->lds_bytes, stream));
 }
 
 }  // namespace

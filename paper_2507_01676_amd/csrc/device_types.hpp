@@ -46,7 +46,8 @@ struct GatherRun {
   int32_t cb;
   int32_t chunk_base;
   int32_t mean;         // 1: the table's bags are averaged
-  int32_t pad[2];
+  int32_t slot_cb;      // cb and chunk_base of the multi-lookup queue as matrix slots walk it
+  int32_t slot_base;    // (plans that may launch them, else 0)
 };
 static_assert(sizeof(GatherRun) == 48, "GatherRun is staged as three 16-byte pieces");
 // The first record of a worker's slot: how its runs split into queues.
@@ -55,7 +56,8 @@ struct GatherSlotHeader {
   int32_t n_single, single_chunks;   // single-lookup-bag runs and their chunks
   int32_t sw_chunks;                 // SW-mode chunks (the remaining runs)
   int32_t n_runs;
-  int32_t pad[6];
+  int32_t slot_chunks;               // the remaining runs' chunks for matrix slots
+  int32_t pad[5];
 };
 static_assert(sizeof(GatherSlotHeader) == sizeof(GatherRun), "a slot header takes one run record");
 constexpr int kStaticLdsReserve = 1024;   // LDS kept for the kernel's static variables
@@ -115,7 +117,8 @@ EMBX_DECL_GATHER(16)
 #undef EMBX_DECL_GATHER
 
 // Host-callable launchers (defined in lookup.hip).  slots: the kernel whose multi-lookup gather
-// queue is cut for wavefronts that sum bags in matrix slots (gather-only fp32 plans, G 2 to 8).
+// queue is walked by wavefronts that sum bags in matrix slots (gather-only plans: fp32 of G 2 to
+// 8, fp16 of G 2 with weights).
 // G = 1 of a gather-only plan: two lanes per row, one in wave mode (16-byte rows).
 int launch_lookup(const LookupArgs& a, int G, bool f16, bool staged, bool weighted, bool slots, int grid,
                   int lds_bytes, void* stream);

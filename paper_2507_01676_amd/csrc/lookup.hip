@@ -30,7 +30,7 @@
 //          three queues of small chunks: long bags (wave mode), bags of at most
 //          one lookup (a chunk of kU bags is one SW step and each row is its
 //          bag's output), and the rest (SW mode, walked as one stream across
-//          chunks; narrow fp32 rows by wavefronts in matrix slots, see Slots).
+//          chunks; narrow rows by wavefronts in matrix slots, see Slots).
 //          Invalid ids read a row of zeros; fp16 halves are added with a
 //          mixed-precision fma.
 //
@@ -49,8 +49,8 @@
 // The lookup kernels are compiled in parts so that a build can run the parts in
 // parallel: EMBX_PART 0..3 holds the kernels of plans with staged slices of one (row type,
 // weighted) pair, 7..10 those of gather-only plans, part 4 the probes, the table filler and
-// the launch code, parts 5 and 6 the fp32 kernels of gather-only plans with rows in matrix
-// slots (their control is wave-uniform, see build.py).  Without EMBX_PART one compile holds
+// the launch code, parts 5, 6 and 11 the fp32, weighted fp32 and weighted fp16 kernels of
+// gather-only plans with rows in matrix slots (their control is wave-uniform, see build.py).  Without EMBX_PART one compile holds
 // everything.
 #ifndef EMBX_PART
 #define EMBX_PART -1
@@ -1528,7 +1528,8 @@ __device__ __forceinline__ void walk_single(GMEM const int64_t* __restrict__ ind
 
 // ---------------------------------------------------------------- gather: narrow rows in matrix slots
 //
-// fp32 rows of 16 to 128 bytes, where the plan says so.  A wavefront takes a chunk of bags of one table,
+// fp32 rows of 16 to 128 bytes and weighted fp16 rows of 16 and 32, where the plan and the launch
+// say so (fp16 elements are widened first).  A wavefront takes a chunk of bags of one table,
 // M = min(4, G) slots per SW: SW s of the S = 64 / G sums m' <= M consecutive bags, so the S
 // SWs walk S streams of lookups side by side and a row load covers S rows through one
 // descriptor.  v_mfma_f32_4x4x1 does the sums: it multiplies 16 blocks of 4 lanes, each D[4][4]
@@ -1570,11 +1571,11 @@ __device__ __forceinline__ int64_t slot_bcast64(int64_t v) {
   return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
 }
 
-template <int G, bool W>
+template <int G, bool F16, bool W>
 struct Slots {
   static_assert(G == 2 || G == 4 || G == 8, "whole SWs per block of 4 lanes, or whole blocks per SW");
   static constexpr int S = kWave / G, M = G < 4 ? G : 4;
-  static constexpr int NA = 4;
+  static constexpr int NA = F16 ? 8 : 4;
   static constexpr int kUS = kSlotStep;       // rows in flight per SW
   static constexpr int IPL = kUS / G;         // ids per lane of a step: lane c holds lookups c, c + G, ...
 
@@ -1601,19 +1602,19 @@ struct Slots {
         c.run = -1;
         return;
       }
-      while (true) {   // the run holding chunk x: chunk_base ascends
+      while (true) {   // the run holding chunk x: slot_base ascends
         const int y = e + 1 + lane;
-        const int passed = __popcll(__ballot(y < e_end && runs[min(y, e_end - 1)].chunk_base <= x));
+        const int passed = __popcll(__ballot(y < e_end && runs[min(y, e_end - 1)].slot_base <= x));
         e = __builtin_amdgcn_readfirstlane(e + passed);
         if (passed < kWave) break;
       }
       const LMEM GatherRun& r = runs[e];
       // floor(j B / k) exactly: j B < 2^47, and a quotient below an integer is below it by 1/k >= 2^-16
       const double B = a.B, j = r.j, k = r.k;
-      const int cb = __builtin_amdgcn_readfirstlane(r.cb);
+      const int cb = __builtin_amdgcn_readfirstlane(r.slot_cb);
       const int bs = __builtin_amdgcn_readfirstlane(static_cast<int>(j * B / k));
       const int be = __builtin_amdgcn_readfirstlane(static_cast<int>((j + 1.0) * B / k));
-      c.c0 = uni(bs + (x - uni(r.chunk_base)) * cb);
+      c.c0 = uni(bs + (x - uni(r.slot_base)) * cb);
       c.c1 = uni(min(be, c.c0 + cb));
       if (c.c0 < c.c1) {
         c.run = uni(e);
@@ -1704,6 +1705,21 @@ struct Slots {
     return __ballot(!(t == 0.0f)) == 0;
   }
 
+  // the NA elements of this lane's 16 bytes of a row
+  static __device__ __forceinline__ void elements(const i32x4 r, float (&x)[NA]) {
+    const int w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (!F16) {
+        x[i] = __int_as_float(w[i]);
+      } else {
+        const uint32_t v = static_cast<uint32_t>(w[i]);
+        x[2 * i] = __half2float(__ushort_as_half(static_cast<unsigned short>(v & 0xffffu)));
+        x[2 * i + 1] = __half2float(__ushort_as_half(static_cast<unsigned short>(v >> 16)));
+      }
+    }
+  }
+
   // Stores the chunk's bags.  Register r of d holds slot r, where a block holds two SWs (G = 2)
   // the registers from hi on this lane's.
   __device__ __forceinline__ void store(const Chunk& c, const Table& t, const Lane& l, int hi, const f32x4 (&d)[NA]) const {
@@ -1713,7 +1729,7 @@ struct Slots {
     if (t.mean && c.en - c.st > 1) scale = 1.0f / static_cast<float>(c.en - c.st);
     static_for<M>([&](auto r) __attribute__((always_inline)) {
       constexpr int rr = decltype(r)::value;
-      Acc<false> acc;
+      Acc<F16> acc;
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         float v = d[i][rr];
@@ -1757,8 +1773,8 @@ struct Slots {
         if (__ballot(in != 0) == 0) return;   // no SW is in this slot
         static_for<kUS>([&](auto u) __attribute__((always_inline)) {
           const float w = W ? __int_as_float(sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0]))) : rb0.one;
-          const float x[NA] = {__int_as_float(raw[u].x), __int_as_float(raw[u].y), __int_as_float(raw[u].z),
-                               __int_as_float(raw[u].w)};
+          float x[NA];
+          elements(raw[u], x);
           const bool on = ((in >> u) & 1u) != 0;
 #pragma unroll
           for (int i = 0; i < NA; ++i) d[i][rr] = on ? __builtin_fmaf(x[i], w, d[i][rr]) : d[i][rr];
@@ -1805,11 +1821,10 @@ struct Slots {
           static_for<kUS>([&](auto u) __attribute__((always_inline)) {
             const int one = W ? sw_bcast<G, u % G>(__float_as_int(wl[W ? u / G : 0])) : 0x3f800000;
             const float f = __int_as_float(__builtin_amdgcn_sbfe(static_cast<int>(in_slot), u, 1) & one);
-            const i32x4 x = raw[u];
-            d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.x), d[0], 0, 0, 0);
-            d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.y), d[1], 0, 0, 0);
-            d[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.z), d[2], 0, 0, 0);
-            d[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, __int_as_float(x.w), d[3], 0, 0, 0);
+            float x[NA];
+            elements(raw[u], x);
+#pragma unroll
+            for (int i = 0; i < NA; ++i) d[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, x[i], d[i], 0, 0, 0);
           });
           if (!more) break;
         }
@@ -1862,7 +1877,7 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
   __syncthreads();
   const LMEM GatherSlotHeader* hd = reinterpret_cast<const LMEM GatherSlotHeader*>(lds);
   const int n_wave = hd->n_wave, wave_chunks = hd->wave_chunks, n_single = hd->n_single,
-            single_chunks = hd->single_chunks, sw_chunks = hd->sw_chunks, nr = hd->n_runs;
+            single_chunks = hd->single_chunks, sw_chunks = SLOTS ? hd->slot_chunks : hd->sw_chunks, nr = hd->n_runs;
   lds += sizeof(GatherRun);
   const LMEM GatherRun* runs = reinterpret_cast<const LMEM GatherRun*>(lds);
   GMEM const int64_t* idx = as_global(a.indices);
@@ -1900,10 +1915,9 @@ __device__ __forceinline__ void gather_phase(const LookupArgs& a, lchar* lds, co
     walk_single<G, F16, W>(idx, offsets, out, a.E, a.B, ost, l.lane_sw, f, q);
   }
   if constexpr (SLOTS) {   // narrow fp32 rows: chunks taken by wavefronts
-    static_assert(!F16, "");
     const int lane = l.tid & (kWave - 1);
-    Slots<G, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
-                  lane, l.sw_w, lane & (Slots<G, W>::M - 1)};
+    Slots<G, F16, W> w{a, runs, n_wave + n_single, nr, sw_chunks, __builtin_amdgcn_readfirstlane(l.wave), qctr,
+                       lane, l.sw_w, lane & (Slots<G, F16, W>::M - 1)};
     if (sw_chunks > 0) w.walk(l, rb0);
   } else {  // SW mode
     RunQueue q{runs, n_wave + n_single, nr, sw_chunks, a.B, true, qctr, l.lane_sw, G, l.sw, NSW};
@@ -2052,12 +2066,15 @@ __global__ void __launch_bounds__(256) fill_kernel(char* dst, int64_t row_begin,
 using KernelFn = void (*)(LookupArgs);
 
 // gather-only kernels whose multi-lookup queue is cut for Slots (G = 1: see pick)
-template <bool W>
+template <bool F16, bool W>
 KernelFn pick_slots(int G) {
-  if (G == 1) return &lookup_kernel<2, false, false, W, true, true>;
-  if (G == 2) return &lookup_kernel<2, false, false, W, true>;
-  if (G == 4) return &lookup_kernel<4, false, false, W, true>;
-  if (G == 8) return &lookup_kernel<8, false, false, W, true>;
+  static_assert(!F16 || W, "");
+  if (G == 1) return &lookup_kernel<2, F16, false, W, true, true>;
+  if (G == 2) return &lookup_kernel<2, F16, false, W, true>;
+  if constexpr (!F16) {
+    if (G == 4) return &lookup_kernel<4, false, false, W, true>;
+    if (G == 8) return &lookup_kernel<8, false, false, W, true>;
+  }
   return nullptr;
 }
 template <bool F16, bool STAGED, bool W>
@@ -2091,6 +2108,7 @@ LookupKernelFn gather_only_kernel_f16(int G);
 LookupKernelFn gather_only_kernel_f16_weighted(int G);
 LookupKernelFn slots_kernel_f32(int G);
 LookupKernelFn slots_kernel_f32_weighted(int G);
+LookupKernelFn slots_kernel_f16_weighted(int G);
 
 #if EMBX_HAS_PART(0)
 LookupKernelFn staged_kernel_f32(int G) { return pick<false, true, false>(G); }
@@ -2118,16 +2136,23 @@ LookupKernelFn gather_only_kernel_f16_weighted(int G) { return pick<true, false,
 #endif
 
 #if EMBX_HAS_PART(5)
-LookupKernelFn slots_kernel_f32(int G) { return pick_slots<false>(G); }
+LookupKernelFn slots_kernel_f32(int G) { return pick_slots<false, false>(G); }
 #endif
 #if EMBX_HAS_PART(6)
-LookupKernelFn slots_kernel_f32_weighted(int G) { return pick_slots<true>(G); }
+LookupKernelFn slots_kernel_f32_weighted(int G) { return pick_slots<false, true>(G); }
+#endif
+#if EMBX_HAS_PART(11)
+LookupKernelFn slots_kernel_f16_weighted(int G) { return pick_slots<true, true>(G); }
 #endif
 #if EMBX_HAS_PART(4)
 namespace {
 
 LookupKernelFn pick_any(int G, bool f16, bool staged, bool weighted, bool slots) {
-  if (slots) return f16 || staged ? nullptr : weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
+  if (slots) {
+    if (staged) return nullptr;
+    if (f16) return weighted ? slots_kernel_f16_weighted(G) : nullptr;
+    return weighted ? slots_kernel_f32_weighted(G) : slots_kernel_f32(G);
+  }
   if (staged) {
     if (f16) return weighted ? staged_kernel_f16_weighted(G) : staged_kernel_f16(G);
     return weighted ? staged_kernel_f32_weighted(G) : staged_kernel_f32(G);

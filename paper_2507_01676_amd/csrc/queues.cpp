@@ -171,16 +171,15 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       left -= d.lookups;
     }
   };
-  // Narrow fp32 rows (2 to 8 lanes) are summed in matrix slots by whole wavefronts or by SWs one
-  // by one.  In slots a chunk is bags of one slice, one or more per SW, so the slices must hold
-  // bags for half of a wavefront's S SWs (1.6M lookups in bags of 8, 30 per slice: 18.1 us
-  // against 25.0; bags of 30, 3 per slice of 800 queries: 19.9 against 15.6).  fp16 rows stay
-  // with the SWs: in slots they also pay conversions, which cost more than the slots save (rows
-  // of 64 and 128 bytes, 26 tables: bags of 2 at 1000 to 3000 queries 5.0-10.4 us by SWs, 6.4-15.0
-  // in slots; bags of 8 at 8192 queries 27.6 against 27.3 and 38.2 against 40.7, and 11.9-12.4
-  // against 14.8-15.2 where such a plan is called with 64 queries; rows of 32 bytes 23.9 / 23.3,
-  // with lognormal lengths 68 / 81, with 64 queries 10.3 / 13.4).
-  if (!wave_gather && !staged && !f16 && (G == 2 || G == 4 || G == 8)) {
+  // Narrow rows are summed in matrix slots by whole wavefronts or by SWs one by one: fp32 rows of
+  // 2 to 8 lanes, fp16 rows of 2 (see launch_slots).  In slots a chunk is bags of one slice, one
+  // or more per SW, so the slices must hold bags for half of a wavefront's S SWs (1.6M lookups in
+  // bags of 8, 30 per slice: 18.1 us against 25.0; bags of 30, 3 per slice of 800 queries: 19.9
+  // against 15.6).  fp16 rows of 64 and 128 bytes stay with the SWs: in slots they also pay
+  // conversions, which cost more than the slots save (26 tables: bags of 2 at 1000 to 3000 queries
+  // 5.0-10.4 us by SWs, 6.4-15.0 in slots; bags of 8 at 8192 queries 27.6 against 27.3 and 38.2
+  // against 40.7, and 11.9-12.4 against 14.8-15.2 where such a plan is called with 64 queries).
+  if (!wave_gather && !staged && (G == 2 || (!f16 && (G == 4 || G == 8)))) {
     const double S = 64.0 / G;
     double bags = 0.0, lookups = 0.0, filled = 0.0;
     for (const Item& d : items)
@@ -288,7 +287,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       else if (q->slots) narrow_chunks(w);
       const double wtarget = std::min(wave_chunk, std::max(1.0, std::floor(Ww / nwaves)));
       gr_ptr[w] = static_cast<int32_t>(gr.size());
-      int64_t base[3] = {0, 0, 0};
+      int64_t base[3] = {0, 0, 0}, slot_base = 0;
       int32_t nrun[3] = {0, 0, 0};
       for (int cls = 0; cls < 3; ++cls) {
         for (int32_t i = wg_ptr[w]; i < wg_ptr[w + 1]; ++i) {
@@ -296,7 +295,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
           if (d.strat != S_GATHER || class_of(d) != cls) continue;
           const double s_t = std::max(1.0, stats[d.table].mean_pooling);
           const int32_t cb = cls == 1 ? (wave_gather ? ksteps * (64 / G) : kChunkSingle)
-                             : cls == 2 && (wave_gather || q->slots) ? item_cb[i]
+                             : cls == 2 && (wave_gather || (q->slots && !f16)) ? item_cb[i]
                                       : static_cast<int32_t>(std::max(1.0, std::floor((cls == 0 ? wtarget : target) / s_t)));
           const int64_t nc = (slice_bags_any(d) + cb - 1) / cb;
           if (nc == 0) continue;
@@ -309,6 +308,11 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
           r.cb = cb;
           r.chunk_base = static_cast<int32_t>(base[cls]);
           r.mean = mean[d.table];
+          if (cls == 2 && q->slots) {
+            r.slot_cb = item_cb[i];
+            r.slot_base = static_cast<int32_t>(slot_base);
+            slot_base += (slice_bags_any(d) + r.slot_cb - 1) / r.slot_cb;
+          }
           gr.push_back(r);
           base[cls] += nc;
           nrun[cls] += 1;
@@ -316,7 +320,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       }
       // the worker's header and runs are copied into LDS (all of a workgroup's LDS but
       // the kernel's own static variables)
-      if (base[0] > INT32_MAX || base[1] > INT32_MAX || base[2] > INT32_MAX ||
+      if (base[0] > INT32_MAX || base[1] > INT32_MAX || base[2] > INT32_MAX || slot_base > INT32_MAX ||
           nrun[0] + nrun[1] + nrun[2] > in.run_cap - 1) {
         return EMB_ERR_UNSUPPORTED;
       }
@@ -330,6 +334,7 @@ int gather_queues(const QueueIn& in, GatherQueues* q) {
       hd.single_chunks = static_cast<int32_t>(base[1]);
       hd.sw_chunks = static_cast<int32_t>(base[2]);
       hd.n_runs = nrun[0] + nrun[1] + nrun[2];
+      hd.slot_chunks = static_cast<int32_t>(slot_base);
     }
     gr_ptr[K] = static_cast<int32_t>(gr.size());
   }
@@ -352,8 +357,9 @@ std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int wave
                         const std::vector<GatherRun>& records) {
   static const char* const names[] = {"wave", "single", "multi"};
   char line[160];
-  std::snprintf(line, sizeof line, "kernel %s lanes %d walker %s steps %d wave_lanes %d\n",
+  std::snprintf(line, sizeof line, "kernel %s lanes %d walker %s weighted %s steps %d wave_lanes %d\n",
                 wave_gather ? "gather_kernel" : "lookup_kernel", plan_lanes(P),
+                wave_gather ? "wavefront" : slots && !P.f16 ? "slots" : "sw",
                 wave_gather ? "wavefront" : slots ? "slots" : "sw", ksteps, wave_lanes);
   std::string s = line;
   for (int w = 0; w < P.K; ++w) {
@@ -362,8 +368,8 @@ std::string queues_text(const PlanOut& P, bool wave_gather, bool slots, int wave
     std::memcpy(&hd, r, sizeof hd);
     for (int i = 0; i < hd.n_runs; ++i) {
       const int cls = i < hd.n_wave ? 0 : i < hd.n_wave + hd.n_single ? 1 : 2;
-      std::snprintf(line, sizeof line, "%d %s %d %d %d %d\n", w, names[cls], r[1 + i].table, r[1 + i].j, r[1 + i].k,
-                    r[1 + i].cb);
+      std::snprintf(line, sizeof line, "%d %s %d %d %d %d %d\n", w, names[cls], r[1 + i].table, r[1 + i].j, r[1 + i].k,
+                    r[1 + i].cb, r[1 + i].slot_cb);
       s += line;
     }
   }

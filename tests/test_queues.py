@@ -18,10 +18,18 @@ def tables(n, mean, most=0):
 @pytest.mark.parametrize("batch", [64, 1000, 4096, 30000])
 @pytest.mark.parametrize("bag", [2.0, 3.0, 4.0, 8.0, 12.0, 30.0])
 @pytest.mark.parametrize("E", [8, 16, 24, 32, 64])
-def test_half_precision_rows_are_summed_by_sub_wavefronts(E, bag, batch):
+def test_half_precision_rows_take_slots_with_weights_on_two_lanes_only(E, bag, batch):
     rows, stats = tables(26, bag)
-    head, _ = queues(rows, E, "f16", stats, batch)
+    head, runs = queues(rows, E, "f16", stats, batch)
     assert head["kernel"] == "lookup_kernel" and head["walker"] == "sw"
+    multi = [r for r in runs if r[1] == "multi"]
+    if E >= 24:
+        assert head["weighted"] == "sw"
+    if E <= 16 and batch == 30000:
+        assert head["weighted"] == "slots"
+    assert all((r[6] > 0) == (head["weighted"] == "slots") for r in multi)
+    if head["weighted"] == "slots":   # the sub-wavefronts keep chunks of their own size
+        assert {r[6] for r in multi} <= {32, 64} and max(r[5] for r in multi) <= 64
 
 
 @pytest.mark.parametrize("E,lanes", [(4, 2), (8, 2), (16, 4), (32, 8)])
